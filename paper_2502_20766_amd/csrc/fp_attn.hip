@@ -44,13 +44,20 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // Block size B (queries per query block = keys per key block) is 128 or 64.  A workgroup
 // is one query block: B/32 waves of 32 query rows.  Keys go through LDS in stages of B/2
 // keys (two stages per key block), each stage made of 32-key MFMA sub-blocks.
-template <int B>
+template <int D, int B>
 struct Geo {
   static constexpr int WAVES = B / 32;
   static constexpr int THREADS = 64 * WAVES;
   static constexpr int KEYS = B / 2;            // keys per stage
   static constexpr int SUB = KEYS / 32;         // 32-key sub-blocks per stage
-  static constexpr int WG_PER_CU = 512 / THREADS;  // two waves per SIMD
+  // Waves per SIMD.  At head dim 64 a stage holds half the MFMAs beside the same softmax, so
+  // two waves leave both pipes waiting on each other's latency; a third fits in 168 registers
+  // (163 used): 64 heads at 32k tokens 1873 -> 1760 us (759 -> 808 TFLOP/s), block 64 1522 ->
+  // 1411.  Four waves at block 128 spill 60 registers.  Head dim 128 needs 233 registers;
+  // 32-key stages fit 168 (5 spilled), which gained 1.5% at 128k tokens and lost 1.5% over
+  // every block at 16k and 40% at 4k.
+  static constexpr int OCC = D == 64 ? 3 : 2;
+  static constexpr int WG_PER_CU = 256 * OCC / THREADS;
 };
 
 __device__ __forceinline__ float wave_pair_max(float x) {
@@ -85,10 +92,10 @@ template <int D, int B>
 struct Stage {
   static constexpr int RB = 2 * D;                 // bytes per key row
   static constexpr int CPR = RB / 16;              // 16-byte chunks per row
-  static constexpr int KEYS = Geo<B>::KEYS;
+  static constexpr int KEYS = Geo<D, B>::KEYS;
   static constexpr int BYTES = KEYS * RB;          // one tile (K or V)
   static constexpr int RPI = 1024 / RB;            // rows written by one wave-wide DMA
-  static constexpr int DMA_PER_WAVE = BYTES / 1024 / Geo<B>::WAVES;
+  static constexpr int DMA_PER_WAVE = BYTES / 1024 / Geo<D, B>::WAVES;
 };
 
 // 16-byte chunk swizzles (XOR, so the same function maps logical <-> physical).
@@ -320,10 +327,10 @@ __device__ __forceinline__ Row uniform_row(const Row &r) {
 }
 
 // First key of stage `half` of key block J in row r, or -1 when the stage has no keys.
-template <int B>
+template <int D, int B>
 __device__ __forceinline__ int stage_first_key(const Row &r, int J, int half) {
   if (J < 0 || J > r.I) return -1;
-  const int k0 = J * B + Geo<B>::KEYS * half;
+  const int k0 = J * B + Geo<D, B>::KEYS * half;
   return k0 < r.n ? k0 : -1;
 }
 
@@ -336,7 +343,7 @@ __device__ __forceinline__ int stage_first_key(const Row &r, int J, int half) {
 // stage's K/V copy) and its first K/V copy is issued at the top of the current row's last
 // stage.
 template <int D, int B>
-__global__ __launch_bounds__(Geo<B>::THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__((Geo<D, B>::THREADS)) __attribute__((amdgpu_waves_per_eu(Geo<D, B>::OCC, Geo<D, B>::OCC)))
 void sparse_fa_fwd(AttnArgs a) {
   using S = Stage<D, B>;
   constexpr int BM = B;                   // queries per workgroup (one query block)
@@ -523,7 +530,7 @@ void sparse_fa_fwd(AttnArgs a) {
     cur = next_row();
     nxt_valid = 0;
   }
-  int k0_next = stage_first_key<B>(cur, cur.J0, 0);
+  int k0_next = stage_first_key<D, B>(cur, cur.J0, 0);
   if (k0_next >= 0) issue(cur, k0_next, 0);
   bf16x8 qf[KS];
   while (true) {
@@ -565,18 +572,18 @@ void sparse_fa_fwd(AttnArgs a) {
       k0_next = -1;
       if (t + 1 < n_stages) {
         if (CB == 0) {
-          k0_next = stage_first_key<B>(cur, J_cur, 1);
+          k0_next = stage_first_key<D, B>(cur, J_cur, 1);
         } else {
           J_cur = J_pre;
           J_pre = ((t >> 1) + 2 < cur.cnt) ? cur.list[(t >> 1) + 2] : -1;
-          k0_next = stage_first_key<B>(cur, J_cur, 0);
+          k0_next = stage_first_key<D, B>(cur, J_cur, 0);
         }
         if (k0_next >= 0) issue(cur, k0_next, CB ^ 1);
       } else {
         fetch_finish();
         if (nxt_valid) {
           const Row nr = next_row();
-          k0_next = stage_first_key<B>(nr, nr.J0, 0);
+          k0_next = stage_first_key<D, B>(nr, nr.J0, 0);
           if (k0_next >= 0) issue(nr, k0_next, CB ^ 1);
         }
       }
@@ -635,7 +642,7 @@ void sparse_fa_fwd(AttnArgs a) {
       };
       // ---- the stage's scores, one running-max update for all its keys, the bf16 weights
       // (P^T steps of 16 keys) and their sum, then O^T += V^T P^T
-      constexpr int SB = Geo<B>::SUB;
+      constexpr int SB = Geo<D, B>::SUB;
       qk_block(std::integral_constant<int, 0>{});
       if constexpr (SB == 2) qk_block(std::integral_constant<int, 1>{});
       if (diag) {
@@ -1012,30 +1019,28 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
     if (a.d == 128) prepare(I128{}, I64{});
     else prepare(I64{}, I64{});
   }
-  // Persistent grid: resident workgroups for two waves per SIMD (a multiple of 8, one
-  // share per XCD), no more than there are items.
+  // Persistent grid: resident workgroups (a multiple of 8, one share per XCD), no more than
+  // there are items; groups are interleaved on an XCD when there are at most kMixItems items
+  // per workgroup.
   const int64_t total = n_g * a.hkv;
-  auto grid = [&](int wg_per_cu) {
-    return (int)std::min<int64_t>((wg_per_cu * cus / 8) * 8, (total + 7) / 8 * 8);
+  auto attend = [&](auto dc, auto bc) {
+    constexpr int D = decltype(dc)::value, B = decltype(bc)::value;
+    // with few rows per workgroup (`mix`) two waves per SIMD: a third one slows the longest
+    // rows, which then decide (64 heads of 64, 8k tokens, block 64: 357 us against 329)
+    const int full = Geo<D, B>::WG_PER_CU * cus;
+    AttnArgs args = a;
+    args.mix = total <= (int64_t)kMixItems * full;
+    const int resident = args.mix ? 512 / Geo<D, B>::THREADS * cus : full;
+    const int grid = (int)std::min<int64_t>(resident / 8 * 8, (total + 7) / 8 * 8);
+    hipLaunchKernelGGL((sparse_fa_fwd<D, B>), dim3(grid), dim3(Geo<D, B>::THREADS), 0, stream,
+                       args);
   };
-  // groups interleaved on an XCD when there are at most kMixItems items per workgroup
-  AttnArgs args = a;
-  args.mix = total <= (int64_t)kMixItems * grid(a.block == 128 ? Geo<128>::WG_PER_CU
-                                                                : Geo<64>::WG_PER_CU);
   if (a.block == 128) {
-    if (a.d == 128)
-      hipLaunchKernelGGL((sparse_fa_fwd<128, 128>), dim3(grid(Geo<128>::WG_PER_CU)),
-                         dim3(Geo<128>::THREADS), 0, stream, args);
-    else
-      hipLaunchKernelGGL((sparse_fa_fwd<64, 128>), dim3(grid(Geo<128>::WG_PER_CU)),
-                         dim3(Geo<128>::THREADS), 0, stream, args);
+    if (a.d == 128) attend(I128{}, I128{});
+    else attend(I64{}, I128{});
   } else {
-    if (a.d == 128)
-      hipLaunchKernelGGL((sparse_fa_fwd<128, 64>), dim3(grid(Geo<64>::WG_PER_CU)),
-                         dim3(Geo<64>::THREADS), 0, stream, args);
-    else
-      hipLaunchKernelGGL((sparse_fa_fwd<64, 64>), dim3(grid(Geo<64>::WG_PER_CU)),
-                         dim3(Geo<64>::THREADS), 0, stream, args);
+    if (a.d == 128) attend(I128{}, I64{});
+    else attend(I64{}, I64{});
   }
   return hipGetLastError();
 }
