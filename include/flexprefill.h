@@ -127,6 +127,11 @@ fp_status fp_select_workspace_size(const fp_shape *shape, const fp_params *param
                                    size_t *bytes);
 fp_status fp_attn_workspace_size(const fp_shape *shape, size_t *bytes);
 
+/* Workspace bytes with which fp_sparse_attn runs short problems fastest: the size above,
+ * which is always enough, and room for the partial results of rows whose lists are divided
+ * among several workgroups.  More workspace than this is not used.  Host only. */
+fp_status fp_attn_workspace_preferred(const fp_shape *shape, size_t *bytes);
+
 /* Host-only argument check used by fp_select (params != NULL) and fp_sparse_attn
  * (params == NULL): shape, parameters and workspace size.  Touches no device. */
 fp_status fp_validate(const fp_shape *shape, const fp_params *params, size_t ws_bytes);

@@ -66,6 +66,7 @@ def lib() -> ctypes.CDLL:
         h.fp_indices_size.argtypes = [S, sz, sz]
         h.fp_select_workspace_size.argtypes = [S, P, sz]
         h.fp_attn_workspace_size.argtypes = [S, sz]
+        h.fp_attn_workspace_preferred.argtypes = [S, sz]
         h.fp_validate.argtypes = [S, P, ctypes.c_size_t]
         h.fp_select.argtypes = [S, vp, vp, P, X, vp, ctypes.c_size_t, vp]
         h.fp_sparse_attn.argtypes = [S, vp, vp, vp, X, vp, vp, ctypes.c_size_t, vp]
@@ -75,7 +76,7 @@ def lib() -> ctypes.CDLL:
         h.fp_last_error.argtypes = []
         h.fp_last_error.restype = ctypes.c_char_p
         for name in ("fp_indices_size", "fp_select_workspace_size", "fp_attn_workspace_size",
-                     "fp_validate", "fp_select", "fp_sparse_attn", "fp_sparse_attn_noalloc"):
+                     "fp_attn_workspace_preferred", "fp_validate", "fp_select", "fp_sparse_attn", "fp_sparse_attn_noalloc"):
             getattr(h, name).restype = ctypes.c_int
         _lib_handle = h
     return _lib_handle
@@ -132,6 +133,15 @@ def attn_workspace_size(shape: Shape) -> int:
     out = ctypes.c_size_t()
     _check(lib().fp_attn_workspace_size(ctypes.byref(shape.c), ctypes.byref(out)),
            "fp_attn_workspace_size")
+    return out.value
+
+
+def attn_workspace_preferred(shape: Shape) -> int:
+    """Workspace with which sparse_attn runs short problems fastest (attn_workspace_size is
+    always enough)."""
+    out = ctypes.c_size_t()
+    _check(lib().fp_attn_workspace_preferred(ctypes.byref(shape.c), ctypes.byref(out)),
+           "fp_attn_workspace_preferred")
     return out.value
 
 
@@ -256,8 +266,8 @@ def sparse_attn(q, k, v, indices: Indices, out=None, workspace=None, stream=None
     _check_tensor(out, "out", 3)
     check_shapes(shape, q=q.shape, k=k.shape, v=v.shape, o=out.shape)
     _check_indices(indices, shape)
-    ws_bytes = attn_workspace_size(shape)
     if workspace is None:
+        ws_bytes = attn_workspace_preferred(shape)
         workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=q.device)
     ic = indices.c()
     _check(lib().fp_sparse_attn(ctypes.byref(shape.c), ctypes.c_void_p(q.data_ptr()),

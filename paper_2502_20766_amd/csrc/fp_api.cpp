@@ -161,6 +161,48 @@ size_t attn_layout(const fp_shape *sh, const Dims &dm) {
          align_up(8 * items) + align_up(16 * items);
 }
 
+// Split plan of a short attention problem in `room` (room_bytes of device workspace; null:
+// any size): fills *out (unit_cap = 0 when the problem is not short, or the room too small)
+// and returns the bytes it takes.
+size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, char *room,
+                  size_t room_bytes, fp::SplitArgs *out) {
+  *out = fp::SplitArgs{};
+  const int nb_total = st.nb_off[st.n_seq], G = hq / hkv;
+  // resident workgroups of 256 CUs: two (head dim 128) or three waves per SIMD
+  const int slots = (d == 64 ? 768 : 512) * 128 / block;
+  const int64_t n_g = (int64_t)G * nb_total;
+  if (10 * n_g * hkv > (int64_t)(block == 64 ? fp::kSplitRows64 : fp::kSplitRows128) * slots)
+    return 0;
+  // units that cutting rows of I + 1 blocks into segments of kSegBlocks can add at most
+  int64_t most = 0;
+  for (int s = 0; s < st.n_seq; ++s)
+    for (int I = 0, nb = st.nb_off[s + 1] - st.nb_off[s]; I < nb; ++I) most += I / fp::kSegBlocks;
+  most *= G;
+  const int64_t part = (int64_t)block * (d + 4) * 4;   // O, then two floats per lane of a row
+  auto layout = [&](int64_t extra, fp::SplitArgs *a) {
+    const int64_t cap = n_g + extra, n_slot = 2 * extra * hkv;
+    const size_t o1 = align_up(16 * cap * hkv), o2 = o1 + align_up(16 * cap * hkv), o3 = o2 + align_up(8 * n_slot);
+    if (a) {
+      a->units = (int4 *)room;
+      a->segs = (int4 *)(room + o1);
+      a->tickets = (int32_t *)(room + o2);
+      a->partials = (unsigned long long *)(room + o3);
+      a->unit_cap = (int)cap;
+      a->extra = (int)extra;
+      a->all = extra == most;
+    }
+    return o3 + part * n_slot;
+  };
+  int64_t extra = (slots + hkv - 1) / hkv < most ? (slots + hkv - 1) / hkv : most;
+  if (n_g + extra > fp::kSplitUnits) return 0;
+  if (room) {                                       // as much of the plan as the room holds
+    while (extra > 0 && layout(extra, nullptr) > room_bytes) extra = extra * 3 / 4;
+    if (layout(extra, nullptr) > room_bytes) return 0;
+    layout(extra, out);
+  }
+  return layout(extra, nullptr);
+}
+
 fp_status hip_fail(hipError_t e, const char *what) {
   snprintf(g_last_error, sizeof(g_last_error), "%s: %s", what, hipGetErrorString(e));
   return FP_ERR_HIP;
@@ -197,6 +239,17 @@ fp_status fp_attn_workspace_size(const fp_shape *shape, size_t *bytes) {
   if (st != FP_OK) return st;
   if (!bytes) return FP_ERR_INVALID_ARG;
   *bytes = attn_layout(shape, dm);
+  return FP_OK;
+}
+
+fp_status fp_attn_workspace_preferred(const fp_shape *shape, size_t *bytes) {
+  Dims dm;
+  fp_status st = check_shape(shape, &dm);
+  if (st != FP_OK) return st;
+  if (!bytes) return FP_ERR_INVALID_ARG;
+  fp::SplitArgs sp;
+  *bytes = attn_layout(shape, dm) + plan_split(dm.st, shape->num_q_heads, shape->num_kv_heads,
+                                                   shape->head_dim, shape->block, nullptr, 0, &sp);
   return FP_OK;
 }
 
@@ -294,6 +347,8 @@ fp_status fp_sparse_attn(const fp_shape *shape, const void *q, const void *k, co
                                        align_up(2 * (size_t)dm.nb_total * shape->num_kv_heads *
                                                 shape->block * shape->head_dim));
   a.sort_recs = (int4 *)((char *)a.sort_keys + align_up(8 * dm.nb_total * shape->num_q_heads));
+  const size_t base = attn_layout(shape, dm);
+  plan_split(dm.st, a.hq, a.hkv, a.d, a.block, (char *)ws + base, ws_bytes - base, &a.split);
   hipError_t e = fp::launch_sparse_attn(a, (hipStream_t)stream);
   return e == hipSuccess ? FP_OK : hip_fail(e, "fp_sparse_attn");
 }

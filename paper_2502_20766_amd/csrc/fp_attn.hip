@@ -224,6 +224,20 @@ struct Row {
 
 constexpr int kChunk = 16;   // consecutive ordered items kept together on one XCD
 constexpr int kMixItems = 8;    // at most this many items per workgroup: groups interleaved
+
+// Device-scope accesses of the split rows' partial results: they go past the L2 of the XCD,
+// so a workgroup on another XCD sees what was stored once the storing wave has waited for
+// it (no cache-wide write-back or invalidation, which would cost the other workgroups
+// their K/V tiles).
+__device__ __forceinline__ void store_dev(unsigned long long *p, float a, float b) {
+  __hip_atomic_store(p, ((unsigned long long)__float_as_uint(b) << 32) | __float_as_uint(a),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_dev(const unsigned long long *p) {
+  const unsigned long long x =
+      __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)x), __uint_as_float((uint32_t)(x >> 32)));
+}
 constexpr float kLazyLog2 = 8.f;  // rise of a row's max (log2 units) that moves its reference
 
 // Item v of XCD x's work queue -> (KV group g, index j into g's ordered items), false once
@@ -342,7 +356,14 @@ __device__ __forceinline__ int stage_first_key(const Row &r, int J, int half) {
 // stages (one dependent step per stage, each step's loads covered by the wait for the
 // stage's K/V copy) and its first K/V copy is issued at the top of the current row's last
 // stage.
-template <int D, int B>
+//
+// With SPLIT (short problems, whose longest rows would otherwise end long after the others)
+// the grid holds one workgroup per unit instead: a unit is a row, or a segment of one row's
+// list.  The workgroups of a split row count themselves in as they end: all but the last
+// store their unnormalised O, reference max and weight sum; the last one waits for those
+// stores (the others do nothing but store by then, so the wait ends) and merges the
+// segments in list order, so the result does not depend on which workgroup came last.
+template <int D, int B, bool SPLIT>
 __global__ __launch_bounds__((Geo<D, B>::THREADS)) __attribute__((amdgpu_waves_per_eu(Geo<D, B>::OCC, Geo<D, B>::OCC)))
 void sparse_fa_fwd(AttnArgs a) {
   using S = Stage<D, B>;
@@ -390,7 +411,18 @@ void sparse_fa_fwd(AttnArgs a) {
   // ---- first row: item blockIdx / 8 of this XCD's queue, read directly
   Row cur;
   cur.valid = 0;
-  {
+  int4 seg = make_int4(0, 0, 0, 1);       // SPLIT: {first list entry, slot, segment, segments}
+  if constexpr (SPLIT) {
+    // unit blockIdx / Hkv of KV group blockIdx % Hkv: with Hkv a divisor of 8 a group keeps
+    // to the same XCDs, and every group's longest units start first
+    const int g = blockIdx.x % a.hkv, j = blockIdx.x / a.hkv;
+    const int4 rec = a.split.units[(int64_t)g * a.split.unit_cap + j];
+    seg = a.split.segs[(int64_t)g * a.split.unit_cap + j];
+    if (rec.y < 0) return;                // past the group's units
+    cur = row_from(g, __builtin_amdgcn_readfirstlane(rec.x), __builtin_amdgcn_readfirstlane(rec.y),
+                   __builtin_amdgcn_readfirstlane(rec.z), __builtin_amdgcn_readfirstlane(rec.w));
+    cur.list += __builtin_amdgcn_readfirstlane(seg.x);
+  } else {
     int g, j;
     if (queue_item(x0, blockIdx.x >> 3, a.hkv, n_g, a.mix, g, j)) {
       const int4 rec = a.items[(int64_t)g * n_g + j];
@@ -521,7 +553,7 @@ void sparse_fa_fwd(AttnArgs a) {
     stage_dma<D, B>(dst, dst + S::BYTES, kb, vt, kv_row, k0, min(S::KEYS, r.n - k0), doff);
   };
 
-  if (!cur.valid) {                       // this XCD's queue had no first item: take one
+  if (!SPLIT && !cur.valid) {             // this XCD's queue had no first item: take one
     take_position();
     fs = 1;
     barrier();
@@ -540,11 +572,13 @@ void sparse_fa_fwd(AttnArgs a) {
     // the next row's queue position and this row's Q fragments load together, and both are
     // retired here: the stage loop then holds no pending register load, so the compiler
     // adds no wait before its MFMAs (which would also wait for the K/V DMA)
-    if (qi < 8) {
-      take_position();
-      fs = 1;
+    if constexpr (!SPLIT) {
+      if (qi < 8) {
+        take_position();
+        fs = 1;
+      }
+      fs = __builtin_amdgcn_readfirstlane(fs);
     }
-    fs = __builtin_amdgcn_readfirstlane(fs);
     load_q(cur, qf);
 #pragma unroll
     for (int k = 0; k < KS; ++k) asm volatile("" : "+v"(qf[k]));
@@ -567,7 +601,7 @@ void sparse_fa_fwd(AttnArgs a) {
       const int k0 = k0_next;
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's DMA of stage t landed
       barrier();                        // ... and every wave's; stage t-1 reads are done
-      fetch_step();
+      if constexpr (!SPLIT) fetch_step();
       // the next stage is the row's next one, or the first stage of the next row
       k0_next = -1;
       if (t + 1 < n_stages) {
@@ -579,7 +613,7 @@ void sparse_fa_fwd(AttnArgs a) {
           k0_next = stage_first_key<D, B>(cur, J_cur, 0);
         }
         if (k0_next >= 0) issue(cur, k0_next, CB ^ 1);
-      } else {
+      } else if constexpr (!SPLIT) {
         fetch_finish();
         if (nxt_valid) {
           const Row nr = next_row();
@@ -680,7 +714,77 @@ void sparse_fa_fwd(AttnArgs a) {
     }
 
     // ---- normalise and store: lane holds query row qrow, d = 32db + 8(v/4) + 4lh + v%4
-    const float l_tot = wave_pair_sum(l_run);
+    float l_tot = wave_pair_sum(l_run);
+    if constexpr (SPLIT) {
+      const int nseg = __builtin_amdgcn_readfirstlane(seg.w);
+      if (nseg > 1) {
+        constexpr int THREADS = Geo<D, B>::THREADS;
+        constexpr int PAIRS = 8 * DB;           // float pairs of O per lane
+        const int slot0 = __builtin_amdgcn_readfirstlane(seg.y);
+        const int own = __builtin_amdgcn_readfirstlane(seg.z);
+        // a slot: [pair][thread] of O, then [thread] of (reference max, weight sum)
+        auto slot_of = [&](int i) {
+          return a.split.partials + (int64_t)(slot0 + i) * (PAIRS + 1) * THREADS + tid;
+        };
+        if (tid == 0)
+          fetch_slot[0] = __hip_atomic_fetch_add(a.split.tickets + 2 * slot0, 1, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (fetch_slot[0] != nseg - 1) {
+          unsigned long long *to = slot_of(own);
+#pragma unroll
+          for (int p = 0; p < PAIRS; ++p)
+            store_dev(to + p * THREADS, oacc[p / 8][2 * (p % 8)], oacc[p / 8][2 * (p % 8) + 1]);
+          store_dev(to + PAIRS * THREADS, m_ref, l_tot);
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+          __syncthreads();
+          if (tid == 0)
+            __hip_atomic_fetch_add(a.split.tickets + 2 * slot0 + 1, 1, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+          return;
+        }
+        if (tid == 0)
+          while (__hip_atomic_load(a.split.tickets + 2 * slot0 + 1, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT) != nseg - 1)
+            __builtin_amdgcn_s_sleep(1);
+        __syncthreads();
+        float m_all = m_ref;
+        for (int i = 0; i < nseg; ++i)
+          if (i != own) m_all = fmaxf(m_all, load_dev(slot_of(i) + PAIRS * THREADS).x);
+        f32x16 sum[DB];
+#pragma unroll
+        for (int i = 0; i < DB; ++i) sum[i] = f32x16{};
+        float l_sum = 0.f;
+        for (int i = 0; i < nseg; ++i) {
+          float2 ml = make_float2(m_ref, l_tot);
+          if (i != own) {
+            const unsigned long long *from = slot_of(i);
+            ml = load_dev(from + PAIRS * THREADS);
+            float2 part[PAIRS];
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) part[p] = load_dev(from + p * THREADS);
+            // a segment without a visible key (reference -inf) has weight 0
+            const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml.x - m_all) * c);
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) {
+              sum[p / 8][2 * (p % 8)] = fmaf(f, part[p].x, sum[p / 8][2 * (p % 8)]);
+              sum[p / 8][2 * (p % 8) + 1] = fmaf(f, part[p].y, sum[p / 8][2 * (p % 8) + 1]);
+            }
+            l_sum = fmaf(f, ml.y, l_sum);
+          } else {
+            const float f = ml.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((ml.x - m_all) * c);
+#pragma unroll
+            for (int d = 0; d < DB; ++d)
+#pragma unroll
+              for (int v = 0; v < 16; ++v) sum[d][v] = fmaf(f, oacc[d][v], sum[d][v]);
+            l_sum = fmaf(f, ml.y, l_sum);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < DB; ++i) oacc[i] = sum[i];
+        l_tot = l_sum;
+      }
+    }
     const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
     if (q0 + qrow < cur.n) {
       uint16_t *op = a.o + ((int64_t)(cur.tok0 + q0 + qrow) * a.hq + cur.h) * D;
@@ -695,7 +799,7 @@ void sparse_fa_fwd(AttnArgs a) {
         }
       }
     }
-    if (!nxt_valid) break;
+    if (SPLIT || !nxt_valid) break;
     cur = next_row();
     nxt_valid = 0;
   }
@@ -936,6 +1040,80 @@ __device__ __forceinline__ void sort_group_items(const SeqTable &st, const int32
 }
 
 
+// The split grid's units of KV group g: its items, those listing more than L blocks cut
+// into segments of about equal length, in the order of the keys above (a segment's key
+// holds its own length and first blocks).  L is the group's share of blocks per resident
+// workgroup, and at least kSegBlocks; with L = W / extra (W the group's listed blocks) the
+// cuts add at most `extra` units and fill at most 2 * extra partial slots.  Unit and slot
+// numbers are handed out as the threads come: they decide the order among equals and where
+// a partial result lies, not its value.
+__device__ __forceinline__ void split_group_items(const SeqTable &st, const int32_t *kb_idx,
+                                                  const int32_t *kb_cnt, int hq, int hkv,
+                                                  int64_t tri_total, const SplitArgs &sp, int g,
+                                                  unsigned long long *key) {
+  __shared__ int total, n_unit, n_slot;
+  const int G = hq / hkv;
+  const int n_g = G * st.nb_off[st.n_seq];
+  const int cap = sp.unit_cap;
+  int np = kSortThreads;
+  while (np < cap) np <<= 1;
+  int4 *rec = reinterpret_cast<int4 *>(key + np);
+  int4 *seg = rec + cap;
+  if (threadIdx.x == 0) {
+    total = 0;
+    n_unit = n_g;
+    n_slot = 0;
+  }
+  __syncthreads();
+  int mine = 0;
+  for (int id = threadIdx.x; id < n_g; id += blockDim.x) {
+    item_key(st, kb_idx, kb_cnt, G, tri_total, g, id, key[id], rec[id]);
+    seg[id] = make_int4(0, 0, 0, 1);
+    mine += rec[id].y;
+  }
+  atomicAdd(&total, mine);
+  __syncthreads();
+  const int L = sp.extra == 0 ? 1 << 30
+                : sp.all      ? kSegBlocks
+                              : max(kSegBlocks, (total + sp.extra - 1) / sp.extra);
+  for (int id = threadIdx.x; id < n_g; id += blockDim.x) {
+    const int4 r = rec[id];
+    const int cnt = r.y;
+    if (cnt <= L) continue;
+    const int nseg = (cnt + L - 1) / L;
+    const int s = (uint32_t)r.x >> 26, kk = (r.x >> 13) & 0x1FFF, I = r.x & 0x1FFF;
+    const int32_t *list = kb_idx + (int64_t)(g * G + kk) * tri_total + st.tri_off[s] +
+                          (int64_t)I * (I + 1) / 2;
+    const int u0 = atomicAdd(&n_unit, nseg - 1);
+    const int slot = g * 2 * sp.extra + atomicAdd(&n_slot, nseg);
+    sp.tickets[2 * slot] = 0;
+    sp.tickets[2 * slot + 1] = 0;
+    for (int j = 0; j < nseg; ++j) {
+      const int a = (int)((int64_t)cnt * j / nseg), b = (int)((int64_t)cnt * (j + 1) / nseg);
+      const int u = j == 0 ? id : u0 + j - 1;
+      const int l0 = list[a], l1 = b - a > 1 ? list[a + 1] : -1;
+      const unsigned long long bucket = (unsigned long long)min((b - a) >> 1, 1023);
+      key[u] = ((1023ull - bucket) << 53) |
+               ((unsigned long long)min((unsigned)l0, 0x1FFFu) << 40) |
+               ((unsigned long long)min((unsigned)l1, 0x1FFFu) << 27) | (unsigned long long)u;
+      rec[u] = make_int4(r.x, b - a, l0, l1);
+      seg[u] = make_int4(a, slot, j, nseg);
+    }
+  }
+  __syncthreads();
+  const int n_u = n_unit;
+  switch (np / kSortThreads) {
+    case 1: sort_keys<1>(key, key, n_u); break;
+    case 2: sort_keys<2>(key, key, n_u); break;
+    default: sort_keys<4>(key, key, n_u); break;
+  }
+  for (int t = threadIdx.x; t < cap; t += blockDim.x) {
+    const int u = t < n_u ? (int)(key[t] & 0x3FFF) : 0;
+    sp.units[(int64_t)g * cap + t] = t < n_u ? rec[u] : make_int4(0, -1, -1, -1);
+    sp.segs[(int64_t)g * cap + t] = seg[u];
+  }
+}
+
 // One launch for both preparations of the attention: workgroups 0 .. Hkv-1 sort their KV
 // group's items (as above), the others (about one per CU the sort leaves) write the V^T
 // tiles, four at a time per workgroup (one per 256 threads).  1024 threads; 128 KB of LDS
@@ -947,10 +1125,14 @@ __global__ __launch_bounds__(1024) void prepare_attn(SeqTable st, const int32_t 
                                                      const unsigned long long *keys,
                                                      const int4 *recs, int4 *items,
                                                      int32_t *queue, const uint16_t *v,
-                                                     int nb_total, uint16_t *vt) {
+                                                     int nb_total, uint16_t *vt, SplitArgs sp) {
   static_assert(4 * B * D * 2 <= kSortItems * 8, "V^T tiles exceed the shared LDS");
   __shared__ __attribute__((aligned(16))) unsigned long long smem[kSortItems];
   if ((int)blockIdx.x < hkv) {
+    if (sp.unit_cap > 0) {
+      split_group_items(st, kb_idx, kb_cnt, hq, hkv, tri_total, sp, blockIdx.x, smem);
+      return;
+    }
     sort_group_items(st, kb_idx, kb_cnt, hq, hkv, tri_total, keys, recs, items, queue,
                      blockIdx.x, smem);
     return;
@@ -1001,7 +1183,8 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
       const int vt_wgs = std::max(1, std::min(cus - a.hkv, groups));
       hipLaunchKernelGGL((prepare_attn<D, B>), dim3(a.hkv + vt_wgs), dim3(1024), 0,
                          stream, a.st, a.kb_idx, a.kb_cnt, a.hq, a.hkv, a.tri_total,
-                         a.sort_keys, a.sort_recs, a.items, a.queue, a.v, a.nb_total, a.vt);
+                         a.sort_keys, a.sort_recs, a.items, a.queue, a.v, a.nb_total, a.vt,
+                         a.split);
     } else {
       hipLaunchKernelGGL(build_item_order_plain, dim3((a.nb_total + 255) / 256), dim3(256), 0,
                          stream, a.st, a.kb_idx, a.kb_cnt, a.hq, a.hkv, a.tri_total, a.items,
@@ -1025,6 +1208,11 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
   const int64_t total = n_g * a.hkv;
   auto attend = [&](auto dc, auto bc) {
     constexpr int D = decltype(dc)::value, B = decltype(bc)::value;
+    if (a.split.unit_cap > 0) {
+      hipLaunchKernelGGL((sparse_fa_fwd<D, B, true>), dim3(a.split.unit_cap * a.hkv),
+                         dim3(Geo<D, B>::THREADS), 0, stream, a);
+      return;
+    }
     // with few rows per workgroup (`mix`) two waves per SIMD: a third one slows the longest
     // rows, which then decide (64 heads of 64, 8k tokens, block 64: 357 us against 329)
     const int full = Geo<D, B>::WG_PER_CU * cus;
@@ -1032,7 +1220,7 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
     args.mix = total <= (int64_t)kMixItems * full;
     const int resident = args.mix ? 512 / Geo<D, B>::THREADS * cus : full;
     const int grid = (int)std::min<int64_t>(resident / 8 * 8, (total + 7) / 8 * 8);
-    hipLaunchKernelGGL((sparse_fa_fwd<D, B>), dim3(grid), dim3(Geo<D, B>::THREADS), 0, stream,
+    hipLaunchKernelGGL((sparse_fa_fwd<D, B, false>), dim3(grid), dim3(Geo<D, B>::THREADS), 0, stream,
                        args);
   };
   if (a.block == 128) {

@@ -86,6 +86,31 @@ struct SelState {
   int32_t pad;
 };
 
+// The split grid is taken for at most this many tenths of a row per resident workgroup.
+// Where the line lies (attention, us, other grid -> split grid): block 128, 2.0 rows
+// (32 heads, 4k tokens) 142 -> 128, 2.9 (6k) 256 -> 246, 4.0 (8k) 344 -> 361; block 64,
+// 4.0 rows (32 heads, 8k) 316 -> 292, 4.6 (64 heads of 64, 7k) 377 -> 310, 4.9 (32 heads,
+// 10k) 540 -> 546.
+constexpr int kSplitRows128 = 30;
+constexpr int kSplitRows64 = 48;
+// Shortest segment that a longer list is cut into: 3, 4 and 6 blocks measure the same within
+// 3% (two heads of 64, 2k tokens: 29.9, 28.8, 28.4 us; 8 heads, 4k: 43.5, 44.6, 44.7).
+constexpr int kSegBlocks = 4;
+constexpr int kSplitUnits = 2816;   // units per KV group: 8 B of key slots (a power of two),
+                                    // 32 B of records each in the sort's 128 KB of LDS
+
+// Short attention problems: one workgroup per unit, a unit being a row's list or a segment
+// of it (unit_cap = 0: not used).
+struct SplitArgs {
+  int4 *units;             // [Hkv][unit_cap] records {row, blocks, first block, second block}
+  int4 *segs;              // [Hkv][unit_cap] {first list entry, first slot, segment, segments}
+  int32_t *tickets;        // [slots][2] per split row: workgroups that ended, and stored
+  unsigned long long *partials;   // [slots] partial results of segments
+  int32_t unit_cap;        // units per KV group, the unused last ones marked empty
+  int32_t extra;           // units per KV group beyond its rows; 2 * extra slots
+  int32_t all;             // `extra` covers every segment of kSegBlocks
+};
+
 struct AttnArgs {
   SeqTable st;
   const uint16_t *q, *k, *v;
@@ -102,6 +127,7 @@ struct AttnArgs {
   uint16_t *vt;            // [Hkv][NB][B * d] workspace: V^T tiles per key block
   unsigned long long *sort_keys;  // [Hkv][G * NB] workspace: items' sort keys
   int4 *sort_recs;         // [Hkv][G * NB] workspace: item records in item-id order
+  SplitArgs split;
 };
 
 // Device address of the current device's fixed scratch array (fp_noalloc.hip).
