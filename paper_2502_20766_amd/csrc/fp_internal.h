@@ -44,6 +44,9 @@ struct SelectArgs {
   int32_t max_budget;      // 0 = no cap
   int32_t qa_mode;         // 0 flattened map (Algorithm 4), 1 per query block
   int32_t vs_granularity;  // 0 token lines (Algorithm 3), 1 block-pooled lines
+  // set by the launcher: every selection problem in one workgroup (no histograms), and the
+  // line marks made by convert_tiles itself (no vs_marks)
+  int32_t small, marks_inline;
   // workspace
   float2 *chunk_stats;     // [ch_total][Hq][block] (max, sum) in log2 units
   float2 *row_stats;       // [n_seq][Hq][block]

@@ -26,6 +26,7 @@
 // and offset blocks of lines (pool_lines), and a selected unit marks the tiles of all its
 // lines.
 #include "fp_internal.h"
+#include "fp_select_dev.h"
 #include "fp_sort.h"
 
 namespace fp {
@@ -43,37 +44,6 @@ constexpr double kFxScale = 281474976710656.0;   // 2^48
 
 __device__ __forceinline__ unsigned long long to_fx(float x) {
   return x > 0.f ? (unsigned long long)((double)x * kFxScale) : 0ull;
-}
-
-struct Problem {
-  const float *scores;
-  int n;
-  bool active;
-};
-
-__device__ __forceinline__ Problem problem_of(const SelectArgs &a, int p) {
-  const int kind = p & 1;
-  const int sh = p >> 1;
-  const int s = sh / a.hq, h = sh % a.hq;
-  const int pat = a.pattern[s * a.hq + h];
-  const int tok0 = a.st.cu[s];
-  const int n = a.st.cu[s + 1] - tok0;
-  Problem pr{nullptr, 0, false};
-  if (pat == FP_PATTERN_VERTICAL_SLASH && a.vs_granularity == 1) {
-    pr.scores = (kind == 0 ? a.av_blk : a.as_blk) + (int64_t)h * a.nb_total + a.st.nb_off[s];
-    pr.n = a.st.nb_off[s + 1] - a.st.nb_off[s];
-    pr.active = true;
-  } else if (pat == FP_PATTERN_VERTICAL_SLASH) {
-    pr.scores = (kind == 0 ? a.a_v : a.a_s) + (int64_t)h * a.total_tokens + tok0;
-    pr.n = n;
-    pr.active = true;
-  } else if (pat == FP_PATTERN_QUERY_AWARE && kind == 0 && a.qa_mode == 0) {
-    const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
-    pr.scores = a.flat + (int64_t)h * a.tri_total + a.st.tri_off[s];
-    pr.n = nb * (nb + 1) / 2;
-    pr.active = true;
-  }
-  return pr;
 }
 
 // Inclusive scan, in thread order over the workgroup, of a (fixed-point mass, count) pair
@@ -121,29 +91,6 @@ __device__ __forceinline__ void block_incl_scan(unsigned long long &m, uint32_t 
 __device__ __forceinline__ bool is_selected(const SelState &S, float x, int id) {
   const uint32_t key = __float_as_uint(x);
   return key > S.key || (key == S.key && id <= S.idcut);
-}
-
-__global__ void sel_init(SelectArgs a) {
-  const int p = blockIdx.x;
-  for (int b = threadIdx.x; b < kHistBuckets; b += blockDim.x) {
-    a.hist_cnt[(int64_t)p * kHistBuckets + b] = 0u;
-    a.hist_mass[(int64_t)p * kHistBuckets + b] = 0ull;
-  }
-  if ((p & 1) == 0) {                     // clear the line marks of this (sequence, head)
-    const int sh = p >> 1, s = sh / a.hq, h = sh % a.hq;
-    const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
-    uint32_t *mk = reinterpret_cast<uint32_t *>(a.vs_marks) +
-                   (int64_t)h * a.nb_total + a.st.nb_off[s];
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) mk[i] = 0u;
-  }
-  if (threadIdx.x == 0) {
-    const Problem pr = problem_of(a, p);
-    SelState S = {};
-    S.mode = pr.active ? 0 : 2;
-    S.n = pr.n;
-    S.idcut = -1;
-    a.sel[p] = S;
-  }
 }
 
 template <int PASS>
@@ -320,60 +267,51 @@ __global__ __launch_bounds__(1024) void sel_tie(SelectArgs a) {
 // three radix passes through an LDS histogram and the lowest-id tie break in the same
 // launch -- one launch instead of the seven above, the same threshold key, counts and
 // tie cut (every sum is an exact integer, so the result does not depend on the path).
+// A thread holds its E scores (units tid + 1024 e) in registers over the passes.  The LDS
+// atomics bound it (many scores share a bucket), so the histogram holds masses only: units
+// of the threshold key all carry that key's own mass, and the units above it are counted
+// once at the end (32 heads: 15.3 -> 11.7 us at 4k tokens, 35.5 -> 26.4 at 16k).
 constexpr int kSmallUnits = 16384;    // largest problem (units) taken by sel_small
 
+template <int E>
 __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
-  __shared__ uint32_t cnt[kHistBuckets];
   __shared__ unsigned long long mass[kHistBuckets];
   __shared__ unsigned long long wmass[16];
-  __shared__ uint32_t wcnt[16];
-  __shared__ SelState sS;
-  __shared__ uint32_t wcount[16];
+  __shared__ unsigned long long s_run;
+  __shared__ uint32_t s_digit, wcount[16];
   __shared__ int found;
-  const int p = blockIdx.x, tid = threadIdx.x;
+  const int p = blockIdx.x, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   SelState S = a.sel[p];
   if (S.mode != 0) return;                // the same decision in every thread
   const Problem pr = problem_of(a, p);
+  float xs[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) xs[e] = tid + 1024 * e < S.n ? pr.scores[tid + 1024 * e] : 0.f;
   const int top = kHistBuckets - 2 * tid; // thread t owns buckets [top - 2, top): thread
                                           // order is descending key order
 #pragma unroll 1
   for (int pass = 0; pass < 3; ++pass) {
     const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
     const uint32_t dmask = pass == 2 ? 1023u : 2047u;
-    for (int b = tid; b < kHistBuckets; b += 1024) {
-      cnt[b] = 0u;
-      mass[b] = 0ull;
-    }
-    if (tid == 0) sS = S;
+    // key bits that the earlier passes fixed
+    const uint32_t fixed = pass == 0 ? 0u : (pass == 1 ? ~0u << 21 : ~0u << 10);
+    mass[tid] = 0ull;
+    mass[tid + 1024] = 0ull;
     __syncthreads();
-    for (int i = tid; i < S.n; i += 1024) {
-      const float x = pr.scores[i];
-      const uint32_t key = __float_as_uint(x);
-      const bool match = pass == 0 || (pass == 1 && (key >> 21) == (S.prefix >> 21)) ||
-                         (pass == 2 && (key >> 10) == (S.prefix >> 10));
-      if (match) {
-        const uint32_t dg = (key >> shift) & dmask;
-        atomicAdd(&cnt[dg], 1u);
-        atomicAdd(&mass[dg], to_fx(x));
-      }
-    }
-    __syncthreads();
-    unsigned long long bm[2];
-    uint32_t bc[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      bm[i] = mass[top - 1 - i];
-      bc[i] = cnt[top - 1 - i];
+    for (int e = 0; e < E; ++e) {
+      const uint32_t key = __float_as_uint(xs[e]);
+      const unsigned long long fx = to_fx(xs[e]);   // 0 past the last unit
+      if (fx != 0ull && ((key ^ S.prefix) & fixed) == 0u)
+        atomicAdd(&mass[(key >> shift) & dmask], fx);
     }
+    __syncthreads();
+    const unsigned long long bm[2] = {mass[top - 1], mass[top - 2]};
     const unsigned long long lm = bm[0] + bm[1];
-    const uint32_t lc = bc[0] + bc[1];
-    unsigned long long im = lm, total_m;
-    uint32_t ic = lc, total_c;
-    block_incl_scan<16>(im, ic, wmass, wcnt, total_m, total_c);
-    const unsigned long long excl_m = im - lm;
-    const uint32_t excl_c = ic - lc;
+    unsigned long long im = lm, total;
+    uint32_t ic = 0u, total_c;
+    block_incl_scan<16>(im, ic, wmass, wcount, total, total_c);
     if (pass == 0) {
-      const unsigned long long total = total_m;
       S.total = total;
       if (total == 0ull) {
         S.mode = 1;
@@ -391,47 +329,55 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
         if (tid == 0) a.sel[p] = S;
         return;
       }
-      if (tid == 0) sS = S;
-      __syncthreads();
     }
-    unsigned long long run = S.mass_above + excl_m;
-    uint32_t runc = S.cnt_above + excl_c;
+    unsigned long long run = S.mass_above + im - lm;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       if (run < S.thr && run + bm[i] >= S.thr) {   // exactly one bucket of all threads
-        SelState T = S;
-        const uint32_t digit = (uint32_t)(top - 1 - i);
-        T.prefix |= digit << shift;
-        T.mass_above = run;
-        T.cnt_above = runc;
-        if (pass == 2) {
-          T.key = T.prefix;
-          T.n_eq = bc[i];
-          const unsigned long long f = bm[i] / bc[i];   // equal keys carry equal mass
-          const unsigned long long need = (T.thr - run + f - 1) / f;
-          T.need_eq = (uint32_t)need;
-          T.k = (int32_t)(runc + need);
-          T.idcut = (need >= bc[i]) ? 0x7FFFFFFF : -1;
-        }
-        sS = T;
+        s_digit = (uint32_t)(top - 1 - i);
+        s_run = run;
       }
       run += bm[i];
-      runc += bc[i];
     }
     __syncthreads();
-    S = sS;
-    __syncthreads();                      // every thread has read sS before it is reused
+    S.prefix |= s_digit << shift;
+    S.mass_above = s_run;
+    __syncthreads();                      // every thread has read them before they are reused
   }
+  S.key = S.prefix;
+  const unsigned long long f = to_fx(__uint_as_float(S.key));
+  S.need_eq = (uint32_t)((S.thr - S.mass_above + f - 1) / f);
+  // units above the key, and of the key (both at most kSmallUnits)
+  uint32_t c = 0u;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t key = __float_as_uint(xs[e]);
+    const bool in = tid + 1024 * e < S.n;
+    c += (in && key > S.key ? 1u << 16 : 0u) + (in && key == S.key ? 1u : 0u);
+  }
+  // (a sum of at most 2^16 units per half does not carry over: S.n <= 2^14)
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if (lane == 0) wcount[w] = c;
+  if (tid == 0) found = -1;
+  __syncthreads();
+  c = 0u;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) c += wcount[k];
+  S.cnt_above = c >> 16;
+  S.n_eq = c & 0xFFFFu;
+  S.k = (int32_t)(S.cnt_above + S.need_eq);
+  S.idcut = 0x7FFFFFFF;
   // lowest-id tie break (as sel_tie), when some but not all units of the key are taken
-  if (S.idcut == -1) {
-    const int w = tid >> 6, lane = tid & 63;
+  if (S.need_eq < S.n_eq) {
     uint32_t running = 0;
-    if (tid == 0) found = -1;
-    __syncthreads();
-    for (int base = 0; base < S.n; base += 1024) {
-      const int i = base + tid;
-      const bool f = i < S.n && __float_as_uint(pr.scores[i]) == S.key;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      if (1024 * e >= S.n) break;
+      const int i = 1024 * e + tid;
+      const bool f = i < S.n && __float_as_uint(xs[e]) == S.key;
       const unsigned long long bal = __ballot(f);
+      __syncthreads();                    // the last reads of wcount and found are done
       if (lane == 0) wcount[w] = (uint32_t)__popcll(bal);
       __syncthreads();
       uint32_t before = 0, chunk = 0;
@@ -441,11 +387,9 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
       }
       const uint32_t rank = running + before + (uint32_t)__popcll(bal & __lanemask_lt());
       if (f && rank + 1 == S.need_eq) found = i;
-      __syncthreads();
-      if (found >= 0) break;
       running += chunk;
-      __syncthreads();
     }
+    __syncthreads();
     S.idcut = found;
   }
   if (tid == 0) a.sel[p] = S;
@@ -453,49 +397,35 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
 
 // ---------------------------------------------------------------- conversion to lists
 
-// Vertical-slash heads: mark, per key block / block diagonal, what the selected lines
-// reach (vertical j: column floor(j/b); slash o = D*b + t: diagonal D in full query blocks,
-// diagonal D in the partial last query block when t < its rows, diagonal D+1 when t > 0).
-// One workgroup per (sequence, head, slice of kMarkSlice lines); the stores only ever
-// write 1, so their order does not matter.
-constexpr int kMarkSlice = 8192;
+// What the selected lines of a vertical-slash head reach, per key block / block diagonal.
+// vertical j: column floor(j/b); slash o = D*b + t: diagonal D in full query blocks, diagonal
+// D in the partial last query block when t < its rows, diagonal D+1 when t > 0.  A mark is
+// only ever set, so the order of the threads does not matter.
+struct LineMarks {
+  uint8_t *col, *d0, *d0p, *d1;
+  int stride;                            // bytes between consecutive key blocks of one array
+  __device__ __forceinline__ void vertical(int J) const { col[J * stride] = 1; }
+  __device__ __forceinline__ void slash(int D, int t, int last_rows, int nb) const {
+    d0[D * stride] = 1;
+    if (t < last_rows) d0p[D * stride] = 1;
+    if (t > 0 && D + 1 < nb) d1[(D + 1) * stride] = 1;
+  }
+};
 
-__global__ __launch_bounds__(256) void vs_marks(SelectArgs a) {
-  const int s = blockIdx.x / a.hq, h = blockIdx.x % a.hq;
-  if (a.pattern[s * a.hq + h] != FP_PATTERN_VERTICAL_SLASH) return;
+// Lines [j0, j1) of one (sequence, head), by nt threads.
+__device__ __forceinline__ void mark_lines(const SelectArgs &a, int s, int h, const SelState S0,
+                                           const SelState S1, int j0, int j1, int tid, int nt,
+                                           const LineMarks &mk) {
   const int tok0 = a.st.cu[s];
   const int n = a.st.cu[s + 1] - tok0;
-  const int b = a.block;
   const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
-  const int last_rows = n - (nb - 1) * b;
-  const int p0 = (s * a.hq + h) * 2;
-  const SelState S0 = a.sel[p0];
-  const SelState S1 = a.sel[p0 + 1];
-  uint8_t *mk = a.vs_marks + 4 * ((int64_t)h * a.nb_total + a.st.nb_off[s]);
-  if (a.vs_granularity == 1) {
-    // a selected unit selects all its lines: key block J is a column; offset block D
-    // holds o = D*b (t = 0: diagonal D in every row) and, when it has more than one
-    // offset, o = D*b + t with t > 0 (diagonal D + 1)
-    const int u = blockIdx.y * blockDim.x + threadIdx.x;
-    if (u >= nb) return;
-    const float *avb = a.av_blk + (int64_t)h * a.nb_total + a.st.nb_off[s];
-    const float *asb = a.as_blk + (int64_t)h * a.nb_total + a.st.nb_off[s];
-    if (is_selected(S0, avb[u], u)) mk[4 * u + 0] = 1;
-    if (is_selected(S1, asb[u], u)) {
-      mk[4 * u + 1] = 1;
-      mk[4 * u + 2] = 1;
-      if (n - u * b > 1 && u + 1 < nb) mk[4 * (u + 1) + 3] = 1;
-    }
-    return;
-  }
+  const int shift = a.block == 64 ? 6 : 7;
+  const int last_rows = n - ((nb - 1) << shift);
   const float *av = a.a_v + (int64_t)h * a.total_tokens + tok0;
   const float *as = a.a_s + (int64_t)h * a.total_tokens + tok0;
-  const int j0 = blockIdx.y * kMarkSlice;
-  const int j1 = min(j0 + kMarkSlice, n);
   // four scores per thread are loaded before any mark is stored (a byte store may alias
   // the scores, so the compiler would otherwise wait for each load in turn)
-  const int nt = blockDim.x;
-  for (int base = j0 + threadIdx.x; base < j1; base += 4 * nt) {
+  for (int base = j0 + tid; base < j1; base += 4 * nt) {
     float xv[4], xs[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -507,15 +437,48 @@ __global__ __launch_bounds__(256) void vs_marks(SelectArgs a) {
     for (int u = 0; u < 4; ++u) {
       const int j = base + u * nt;
       if (j >= j1) break;
-      if (is_selected(S0, xv[u], j)) mk[4 * (j / b) + 0] = 1;
-      if (is_selected(S1, xs[u], j)) {
-        const int dl = j / b, t = j % b;
-        mk[4 * dl + 1] = 1;
-        if (t < last_rows) mk[4 * dl + 2] = 1;
-        if (t > 0 && dl + 1 < nb) mk[4 * (dl + 1) + 3] = 1;
-      }
+      if (is_selected(S0, xv[u], j)) mk.vertical(j >> shift);
+      if (is_selected(S1, xs[u], j)) mk.slash(j >> shift, j & (a.block - 1), last_rows, nb);
     }
   }
+}
+
+// Block-pooled lines: a selected unit selects all its lines.  Key block J is a column;
+// offset block D holds o = D*b (t = 0: diagonal D in every row) and, when it has more than
+// one offset, o = D*b + t with t > 0 (diagonal D + 1).
+__device__ __forceinline__ void mark_blocks(const SelectArgs &a, int s, int h, const SelState S0,
+                                            const SelState S1, int tid, int nt,
+                                            const LineMarks &mk) {
+  const int n = a.st.cu[s + 1] - a.st.cu[s];
+  const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
+  const float *avb = a.av_blk + (int64_t)h * a.nb_total + a.st.nb_off[s];
+  const float *asb = a.as_blk + (int64_t)h * a.nb_total + a.st.nb_off[s];
+  for (int u = tid; u < nb; u += nt) {
+    if (is_selected(S0, avb[u], u)) mk.vertical(u);
+    if (is_selected(S1, asb[u], u)) {
+      mk.slash(u, 0, 1, nb);
+      if (n - u * a.block > 1 && u + 1 < nb) mk.d1[(u + 1) * mk.stride] = 1;
+    }
+  }
+}
+
+// Marks of long sequences' lines, one workgroup per (sequence, head, slice of kMarkSlice
+// lines).  convert_tiles makes its own where every workgroup can afford to read the head's
+// scores: sequences of up to kMarkInline tokens, and block-pooled lines of any length.
+constexpr int kMarkSlice = 8192;
+constexpr int kMarkInline = 8192;
+
+__global__ __launch_bounds__(256) void vs_marks(SelectArgs a) {
+  const int s = blockIdx.x / a.hq, h = blockIdx.x % a.hq;
+  if (a.pattern[s * a.hq + h] != FP_PATTERN_VERTICAL_SLASH) return;
+  const int n = a.st.cu[s + 1] - a.st.cu[s];
+  const int p0 = (s * a.hq + h) * 2;
+  const int j0 = blockIdx.y * kMarkSlice;
+  uint8_t *mk = a.vs_marks + 4 * ((int64_t)h * a.nb_total + a.st.nb_off[s]);
+  const SelState S0 = a.sel[p0];
+  const SelState S1 = a.sel[p0 + 1];
+  mark_lines(a, s, h, S0, S1, j0, min(j0 + kMarkSlice, n), threadIdx.x,
+             blockDim.x, LineMarks{mk, mk + 1, mk + 2, mk + 3, 4});
 }
 
 // Lists of one (sequence, head): grid (sequence * head, row slice); wave w of slice r
@@ -543,7 +506,17 @@ __global__ __launch_bounds__(1024) void convert_tiles(SelectArgs a) {
   (void)n;
   if (slice * 16 >= nb) return;                 // no row of this (sequence, head) here
 
-  if (vs) {
+  if (vs && a.marks_inline) {
+    for (int i = tid; i <= nb; i += blockDim.x) {
+      if (i < nb) colsel[i] = d0[i] = d0p[i] = 0;
+      d1[i] = 0;
+    }
+    __syncthreads();
+    const LineMarks mk{colsel, d0, d0p, d1, 1};
+    if (a.vs_granularity == 1) mark_blocks(a, s, h, S0, S1, tid, blockDim.x, mk);
+    else mark_lines(a, s, h, S0, S1, 0, n, tid, blockDim.x, mk);
+    __syncthreads();
+  } else if (vs) {
     const uint32_t *mk = reinterpret_cast<const uint32_t *>(a.vs_marks) +
                          (int64_t)h * a.nb_total + a.st.nb_off[s];
     for (int i = tid; i < nb; i += blockDim.x) {
@@ -961,25 +934,31 @@ hipError_t launch_dense_lists(const SelectArgs &a, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_select_pipeline(const SelectArgs &a, hipStream_t stream) {
+hipError_t launch_select_pipeline(const SelectArgs &args, hipStream_t stream) {
+  SelectArgs a = args;
+  int max_units = 0, max_n = 0;
+  for (int s = 0; s < a.st.n_seq; ++s) {
+    const int n = a.st.cu[s + 1] - a.st.cu[s];
+    const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
+    max_units = max(max_units, max(n, nb * (nb + 1) / 2));
+    max_n = max(max_n, n);
+  }
+  a.marks_inline = a.vs_granularity == 1 || max_n <= kMarkInline;
+  a.small = max_units <= kSmallUnits;
   hipError_t e;
   if ((e = launch_rep_scores(a, stream)) != hipSuccess) return e;
   if ((e = launch_pattern_search(a, stream)) != hipSuccess) return e;
   if ((e = launch_pool_q_query_aware(a, stream)) != hipSuccess) return e;
   if ((e = launch_qa_estimate(a, stream)) != hipSuccess) return e;
   const int problems = a.st.n_seq * a.hq * 2;
-  int max_units = 0;
-  for (int s = 0; s < a.st.n_seq; ++s) {
-    const int n = a.st.cu[s + 1] - a.st.cu[s];
-    const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
-    max_units = max(max_units, max(n, nb * (nb + 1) / 2));
-  }
   const int slices = (max_units + kSlice - 1) / kSlice;
   if (a.vs_granularity == 1)
     hipLaunchKernelGGL(pool_lines, dim3((a.nb_total + 3) / 4, a.hq), dim3(256), 0, stream, a);
-  hipLaunchKernelGGL(sel_init, dim3(problems), dim3(256), 0, stream, a);
-  if (max_units <= kSmallUnits) {
-    hipLaunchKernelGGL(sel_small, dim3(problems), dim3(1024), 0, stream, a);
+  if (a.small) {
+    if (max_units <= 4096)
+      hipLaunchKernelGGL(sel_small<4>, dim3(problems), dim3(1024), 0, stream, a);
+    else
+      hipLaunchKernelGGL(sel_small<16>, dim3(problems), dim3(1024), 0, stream, a);
   } else {
     hipLaunchKernelGGL(sel_hist<0>, dim3(slices, problems), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sel_scan<0>, dim3(problems), dim3(256), 0, stream, a);
@@ -990,11 +969,9 @@ hipError_t launch_select_pipeline(const SelectArgs &a, hipStream_t stream) {
     hipLaunchKernelGGL(sel_tie, dim3(problems), dim3(1024), 0, stream, a);
   }
   {
-    int max_n = 0;
-    for (int s = 0; s < a.st.n_seq; ++s) max_n = max(max_n, a.st.cu[s + 1] - a.st.cu[s]);
-    const int mark_slices = a.vs_granularity == 1 ? (a.st.max_nb + 255) / 256
-                                                  : (max_n + kMarkSlice - 1) / kMarkSlice;
-    hipLaunchKernelGGL(vs_marks, dim3(a.st.n_seq * a.hq, mark_slices), dim3(256), 0, stream, a);
+    if (!a.marks_inline)
+      hipLaunchKernelGGL(vs_marks, dim3(a.st.n_seq * a.hq, (max_n + kMarkSlice - 1) / kMarkSlice),
+                         dim3(256), 0, stream, a);
     // row slices: about two workgroups per CU over all (sequence, head) pairs, and at
     // most four rows per wave on the longest sequence (packed batches mix lengths, and
     // the workgroups of short sequences end early)

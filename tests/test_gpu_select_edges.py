@@ -1,0 +1,51 @@
+"""Selection at the sizes where its launches change: whole rows of the pooled map in one tile
+(up to 128 key blocks), the pattern search in one workgroup (up to 128), line marks made by
+the list conversion (up to 8192 tokens), every selection problem in one workgroup (up to
+16384 units), against the oracle."""
+import pytest
+
+import synth
+from parity import (O_MAX_ABS, O_MEAN_ABS, assert_relaxations_bounded, compare_outputs,
+                    compare_selection, log, to_device)
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+BASE = synth.SPECS["llama32k"].with_params(hq=4, hkv=2, d=64, head_kinds=("vs", "qa") * 2)
+
+# (seqlens, block, vs_granularity)
+CASES = [
+    ((8192,), 64, 0),            # 128 blocks, 8192 lines
+    ((8193, 700), 64, 0),        # 129 blocks, 8193 lines
+    ((11520, 3), 64, 0),         # 180 blocks: 16290 units
+    ((11521,), 64, 0),           # 181 blocks: 16471 units
+    ((16384, 130), 128, 0),      # 128 blocks, 16384 lines
+    ((16385,), 128, 0),          # 129 blocks, 16385 lines
+    ((4096, 4097), 128, 0),      # four and five scores per thread
+    ((16385, 65), 128, 1),       # block-pooled lines of a long sequence
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"{c[0]}-b{c[1]}-g{c[2]}" for c in CASES])
+def test_selection_at_the_edges_of_its_launches(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2502_20766_amd as fpx
+    seqlens, block, vsg = case
+    log(f"[select edges] {case}")
+    spec = BASE.with_seqlens(seqlens, f"edge-{seqlens}-{block}").with_params(block=block)
+    layer = synth.make_layer(spec)
+    q, k, v = to_device(layer)
+    idx = fpx.select(q, k, layer.cu_seqlens, spec.gamma, spec.tau, spec.min_budget, block=block,
+                     vs_granularity=vsg)
+    o = fpx.sparse_attn(q, k, v, idx)
+    torch.cuda.synchronize()
+    g = dict(masks=fpx.masks_from_indices(idx), pattern=idx.pattern.cpu().numpy(),
+             js=idx.js.cpu().numpy(), units=idx.units.cpu().numpy(), o=o.float().cpu().numpy(),
+             idx=idx)
+    st = compare_selection(layer, g, spec.gamma, spec.tau, spec.min_budget, vs_granularity=vsg)
+    log(f"  {st}")
+    assert_relaxations_bounded(st)
+    mx, mean = compare_outputs(layer, g["o"], g["masks"], rows_per_head=3)
+    assert mx <= O_MAX_ABS and mean <= O_MEAN_ABS
