@@ -47,6 +47,8 @@ struct SelectArgs {
   // set by the launcher: every selection problem in one workgroup (no histograms), and the
   // line marks made by convert_tiles itself (no vs_marks)
   int32_t small, marks_inline;
+  // set by the launchers: the line pass merges the chunk statistics, and pools Q
+  int32_t merge_inline, pool_inline;
   // workspace
   float2 *chunk_stats;     // [ch_total][Hq][block] (max, sum) in log2 units
   float2 *row_stats;       // [n_seq][Hq][block]
@@ -112,6 +114,7 @@ struct SplitArgs {
   int32_t unit_cap;        // units per KV group, the unused last ones marked empty
   int32_t extra;           // units per KV group beyond its rows; 2 * extra slots
   int32_t all;             // `extra` covers every segment of kSegBlocks
+  int32_t resident;        // all units run at the same time
 };
 
 struct AttnArgs {

@@ -207,8 +207,8 @@ __global__ __launch_bounds__(kDecideThreads) void pattern_decide(SelectArgs a) {
 // of 8.0 + 6.0 at 128 (32 heads); at 256 blocks it took 19-20 us, the two launches 17.  Grid
 // (n_seq, Hq).
 constexpr int kPatFused = 128;
-template <int D>
-__global__ __launch_bounds__(kDecideThreads) void pattern_search(SelectArgs a) {
+template <int D, int NT>
+__global__ __launch_bounds__(NT) void pattern_search(SelectArgs a) {
   __shared__ __attribute__((aligned(16))) float qbar[D];
   __shared__ float qpart[256 / (D / 8) * D];
   __shared__ float lg[kPatFused];
@@ -217,12 +217,12 @@ __global__ __launch_bounds__(kDecideThreads) void pattern_search(SelectArgs a) {
   const int s = blockIdx.x, h = blockIdx.y;
   const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
   pool_qhat<D>(a, s, h, qpart, qbar);
-  block_terms<D, kDecideThreads>(a, s, h, 0, nb, qbar, [&](int J, float logit, double ahat) {
+  block_terms<D, NT>(a, s, h, 0, nb, qbar, [&](int J, float logit, double ahat) {
     lg[J] = logit;
     ah[J] = ahat;
   });
   __syncthreads();
-  decide<kDecideThreads>(a, s, h, nb, lg, ah, scr);
+  decide<NT>(a, s, h, nb, lg, ah, scr);
 }
 
 // ---------------------------------------------------------------- Algorithm 4 estimate
@@ -253,8 +253,11 @@ __device__ __forceinline__ void row_softmax(const float *x, float *y, int I, int
     if (lane + 64 * u <= I) y[lane + 64 * u] = xv[u] * inv;
 }
 
-constexpr int QT = 128;  // rows and columns of A_bar per workgroup tile
-constexpr int kLogitThreads = 1024;   // 16 waves, one 32x32 block each
+// rows and columns of A_bar per workgroup tile: QT (16 waves, one 32x32 block each), or, where
+// every sequence has at most kQtSmall blocks, one 32x32 block (four waves for the staging and
+// the softmax, a quarter of the LDS)
+constexpr int QT = 128;
+constexpr int kQtSmall = 32;
 
 // Tile (TI, TJ), TJ <= TI, of the logits scale * Q_bar_I . K_bar_J written into the
 // flattened causal layout.  Grid x enumerates the causal tile pairs of all sequences.
@@ -266,8 +269,11 @@ constexpr int kLogitThreads = 1024;   // 16 waves, one 32x32 block each
 // ROWS (every sequence in one tile, i.e. at most QT blocks): the tile holds whole rows of the
 // map, so their softmax is taken here, over an LDS copy, with the operations of qa_softmax:
 // 7.8 us instead of 6.5 + 4.8 at 32 blocks, 21.4 instead of 14.2 + 6.8 at 128 (32 heads).
-template <int D, bool ROWS>
-__global__ __launch_bounds__(kLogitThreads) void qa_logits(SelectArgs a) {
+template <int D, int QT, bool ROWS>
+__global__ __launch_bounds__(QT == 128 ? 1024 : 256) void qa_logits(SelectArgs a) {
+  constexpr int NT = QT == 128 ? 1024 : 256;
+  constexpr int W = QT / 32;             // 32x32 blocks per side
+
   typedef float f32x16 __attribute__((ext_vector_type(16)));
   constexpr int P = D + 4;               // LDS row pitch in floats (16-byte rows, no conflicts)
   __shared__ __attribute__((aligned(16))) float rows[2 * QT * P];
@@ -296,12 +302,12 @@ __global__ __launch_bounds__(kLogitThreads) void qa_logits(SelectArgs a) {
   // stage the rows (rows past the sequence's last block are clamped; their logits are not
   // written)
   // (every load is issued before the first store, so the loads overlap)
-  constexpr int NST = QT * (D / 4) / kLogitThreads;
-  static_assert(NST * kLogitThreads == QT * (D / 4), "staging covers the tile exactly");
+  constexpr int NST = QT * (D / 4) / NT;
+  static_assert(NST * NT == QT * (D / 4), "staging covers the tile exactly");
   float4 qv4[NST], kv4[NST];
 #pragma unroll
   for (int u = 0; u < NST; ++u) {
-    const int i = tid + u * kLogitThreads;
+    const int i = tid + u * NT;
     const int row = i / (D / 4), c = i % (D / 4);
     const int I = min(TI * QT + row, nb - 1), J = min(TJ * QT + row, nb - 1);
     qv4[u] = reinterpret_cast<const float4 *>(
@@ -311,15 +317,16 @@ __global__ __launch_bounds__(kLogitThreads) void qa_logits(SelectArgs a) {
   }
 #pragma unroll
   for (int u = 0; u < NST; ++u) {
-    const int i = tid + u * kLogitThreads;
+    const int i = tid + u * NT;
     const int row = i / (D / 4), c = i % (D / 4);
     *reinterpret_cast<float4 *>(Qs + row * P + 4 * c) = qv4[u];
     *reinterpret_cast<float4 *>(Ks + row * P + 4 * c) = kv4[u];
   }
   __syncthreads();
-  const int i0 = 32 * (w >> 2), j0 = 32 * (w & 3);          // block within the tile
+  const int i0 = 32 * (w / W), j0 = 32 * (w % W);           // block within the tile
   const int I0 = TI * QT + i0, J0 = TJ * QT + j0;
-  const bool used = J0 <= I0 + 31 && I0 < nb;   // not above the diagonal or past the end
+  // not above the diagonal or past the end
+  const bool used = w < W * W && J0 <= I0 + 31 && I0 < nb;
   if (!ROWS && !used) return;
   const float *qa = Qs + (i0 + lr) * P + lh * (D / 2);
   const float *kb = Ks + (j0 + lr) * P + lh * (D / 2);
@@ -345,8 +352,8 @@ __global__ __launch_bounds__(kLogitThreads) void qa_logits(SelectArgs a) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) L[(I0 + 8 * (v >> 2) + 4 * lh + (v & 3)) * LP + J] = acc[v] * a.scale;
     __syncthreads();
-    for (int I = w; I < nb; I += kLogitThreads / 64)
-      row_softmax<QT / 64>(L + I * LP, flat + (int64_t)I * (I + 1) / 2, I, lane);
+    for (int I = w; I < nb; I += NT / 64)
+      row_softmax<(QT + 63) / 64>(L + I * LP, flat + (int64_t)I * (I + 1) / 2, I, lane);
     return;
   }
 #pragma unroll
@@ -384,13 +391,29 @@ __global__ __launch_bounds__(kThreads) void qa_softmax(SelectArgs a) {
 
 }  // namespace
 
+// Sequences of few blocks, and either very few or so many (sequence, head) pairs that
+// workgroups of 1024 threads come one or two to a CU: 256 threads (64 sequences of 8 heads of
+// up to 18 blocks: pattern search 18.1 -> 11.0 us, logits 30.3 -> 14.6; 32 heads of 32 blocks are
+// 2.4 us faster with 1024).
+static bool small_heads(const SelectArgs &a) {
+  return a.st.max_nb <= 16 || (a.st.max_nb <= kQtSmall && a.st.n_seq * a.hq > 256);
+}
+
 hipError_t launch_pattern_search(const SelectArgs &a, hipStream_t stream) {
   if (a.st.max_nb <= kPatFused) {
     const dim3 grid(a.st.n_seq, a.hq);
-    if (a.d == 128)
-      hipLaunchKernelGGL(pattern_search<128>, grid, dim3(kDecideThreads), 0, stream, a);
-    else
-      hipLaunchKernelGGL(pattern_search<64>, grid, dim3(kDecideThreads), 0, stream, a);
+    if (small_heads(a)) {
+      if (a.d == 128)
+        hipLaunchKernelGGL((pattern_search<128, 256>), grid, dim3(256), 0, stream, a);
+      else
+        hipLaunchKernelGGL((pattern_search<64, 256>), grid, dim3(256), 0, stream, a);
+    } else if (a.d == 128) {
+      hipLaunchKernelGGL((pattern_search<128, kDecideThreads>), grid, dim3(kDecideThreads), 0,
+                         stream, a);
+    } else {
+      hipLaunchKernelGGL((pattern_search<64, kDecideThreads>), grid, dim3(kDecideThreads), 0,
+                         stream, a);
+    }
     return hipGetLastError();
   }
   const dim3 parts(a.st.n_seq * kPatSlices, a.hq);
@@ -410,20 +433,19 @@ hipError_t launch_qa_estimate(const SelectArgs &a, hipStream_t stream) {
     const int nt = (nb + QT - 1) / QT;
     pairs += nt * (nt + 1) / 2;
   }
-  const bool rows = a.st.max_nb <= QT;
-  auto logits = [&](auto dc, auto rc) {
-    hipLaunchKernelGGL((qa_logits<decltype(dc)::value, decltype(rc)::value>), dim3(pairs, a.hq),
-                       dim3(kLogitThreads), 0, stream, a);
+  const bool rows = a.st.max_nb <= QT, small = small_heads(a);
+  auto logits = [&](auto dc) {
+    constexpr int D = decltype(dc)::value;
+    const dim3 grid(pairs, a.hq);
+    if (small)
+      hipLaunchKernelGGL((qa_logits<D, kQtSmall, true>), grid, dim3(256), 0, stream, a);
+    else if (rows)
+      hipLaunchKernelGGL((qa_logits<D, QT, true>), grid, dim3(1024), 0, stream, a);
+    else
+      hipLaunchKernelGGL((qa_logits<D, QT, false>), grid, dim3(1024), 0, stream, a);
   };
-  using I128 = std::integral_constant<int, 128>;
-  using I64 = std::integral_constant<int, 64>;
-  if (a.d == 128) {
-    if (rows) logits(I128{}, std::true_type{});
-    else logits(I128{}, std::false_type{});
-  } else {
-    if (rows) logits(I64{}, std::true_type{});
-    else logits(I64{}, std::false_type{});
-  }
+  if (a.d == 128) logits(std::integral_constant<int, 128>{});
+  else logits(std::integral_constant<int, 64>{});
   if (!rows)
     hipLaunchKernelGGL(qa_softmax, dim3((a.nb_total + 3) / 4, a.hq), dim3(kThreads), 0, stream, a);
   return hipGetLastError();

@@ -16,6 +16,7 @@
 // Block pooling (avgpool with window block_size, aligned at token 0 of each sequence): K̄
 // (every KV head) is summed by pass 1 from the K tiles it streams anyway, Q̄ (query-aware
 // heads only) by a separate streaming kernel.
+#include <algorithm>
 #include <type_traits>
 
 #include "fp_internal.h"
@@ -28,6 +29,9 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
 constexpr int KT = 64;             // keys per tile of the statistics pass
+// Rows of at most this many chunks are merged by the line pass itself, which saves the launch
+// of the merge (4.6 us, 18 us for 64 sequences of 8 heads) and adds 0.1-0.9 us.
+constexpr int kMergeInline = 16;
 
 __device__ __forceinline__ int seq_of_chunk(const SeqTable &st, int c) {
   int s = 0;
@@ -145,14 +149,16 @@ __global__ __launch_bounds__(64 * RW * HG) void rep_stats(SelectArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t Ks[KT * D];
   __shared__ float kpart[NSLOT][D];          // per wave: sums over its keys of the block
   const int c = blockIdx.x;
-  const int h = blockIdx.y * HG + (int)threadIdx.x / (64 * RW);
+  // (the wave's number made scalar: branches on its rows must not become selects in every lane)
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = blockIdx.y * HG + wv / RW;
   const int s = seq_of_chunk(a.st, c);
   const int tok0 = a.st.cu[s];
   const int n = a.st.cu[s + 1] - tok0;
   const int bp = min(a.block, n);
   const int c0 = (c - a.st.ch_off[s]) * a.st.ch_len;
   const int c1 = min(c0 + a.st.ch_len, n);
-  const int tid = threadIdx.x, w = (tid >> 6) % RW, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int tid = threadIdx.x, w = wv % RW, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
   const int r = 32 * w + lr;                 // representative row of this lane
   const int irow = n - bp + r;               // its absolute position i_r
   const int G = a.hq / a.hkv;
@@ -291,6 +297,55 @@ __global__ __launch_bounds__(256) void rep_stats_combine(SelectArgs a) {
   if (lane == 0) a.row_stats[((int64_t)s * a.hq + h) * a.block + r] = acc;
 }
 
+// ---------------------------------------------------------------- block pooling
+
+// out[(blk) * H + head][d] = mean over the block's tokens of x[token][head][d], by NT threads;
+// part: NT * 8 floats of LDS.
+template <int D, int NT>
+__device__ __forceinline__ void pool_block(const SeqTable &st, const uint16_t *x, int H, int block,
+                                           float *out, int s, int blk, int head, float *part) {
+  constexpr int CH = D / 8;              // 16-byte chunks per row
+  constexpr int PH = NT / CH;            // token phases
+  const int tok0 = st.cu[s];
+  const int n = st.cu[s + 1] - tok0;
+  const int J = blk - st.nb_off[s];
+  const int t0 = J * block;
+  const int cntk = min(block, n - t0);
+  const int tid = threadIdx.x, ch = tid % CH, ph = tid / CH;
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  for (int t = ph; t < cntk; t += PH) {
+    const uint4 v = *reinterpret_cast<const uint4 *>(x + ((int64_t)(tok0 + t0 + t) * H + head) * D +
+                                                     ch * 8);
+    const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[2 * i] += __uint_as_float(wv[i] << 16);
+      acc[2 * i + 1] += __uint_as_float(wv[i] & 0xFFFF0000u);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) part[ph * D + ch * 8 + i] = acc[i];
+  __syncthreads();
+  if (tid < D) {
+    float sum = 0.f;
+    for (int p = 0; p < PH; ++p) sum += part[p * D + tid];
+    out[((int64_t)blk * H + head) * D + tid] = sum / (float)cntk;
+  }
+}
+
+// Launched with grid (NB, H); heads whose pattern differs from `only_pattern` are skipped.
+template <int D>
+__global__ __launch_bounds__(kThreads) void pool_blocks(SeqTable st, const uint16_t *x, int H,
+                                                        int block, float *out,
+                                                        const uint8_t *pattern, int hq,
+                                                        int only_pattern) {
+  __shared__ float part[kThreads * 8];
+  const int blk = blockIdx.x, head = blockIdx.y;
+  const int s = seq_of_block(st, blk);
+  if (pattern[s * hq + head] != only_pattern) return;
+  pool_block<D, kThreads>(st, x, H, block, out, s, blk, head, part);
+}
+
 // ---------------------------------------------------------------- pass 2: line sums
 
 // 32-key tiles: each of the RW waves (one per 32 representative rows: 4 at block 128, 2 at
@@ -317,13 +372,21 @@ __global__ __launch_bounds__(64 * RW) __attribute__((amdgpu_waves_per_eu(RW))) v
   __shared__ float red[RW][LKT];               // per wave: column sums of the tile
   const int c = blockIdx.x;
   const int h = blockIdx.y;
+  if (c >= a.st.ch_off[a.st.n_seq]) {
+    // (pool_inline) the workgroups past the chunks pool one block of this head's queries
+    const int blk = c - a.st.ch_off[a.st.n_seq];
+    static_assert(NT * 8 <= (LPAD + ROWS + LPAD) * LPITCH, "pooling fits in the weight tile");
+    pool_block<D, NT>(a.st, a.q, a.hq, a.block, a.qbar, seq_of_block(a.st, blk), blk, h, Pt);
+    return;
+  }
   const int s = seq_of_chunk(a.st, c);
   const int tok0 = a.st.cu[s];
   const int n = a.st.cu[s + 1] - tok0;
   const int bp = min(a.block, n);
   const int c0 = (c - a.st.ch_off[s]) * a.st.ch_len;
   const int c1 = min(c0 + a.st.ch_len, n);
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, lr = lane & 31, lh = lane >> 5;
+  const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63,
+            lr = lane & 31, lh = lane >> 5;
   const int r = 32 * w + lr;
   const int G = a.hq / a.hkv;
   const int64_t kv_row = (int64_t)a.hkv * D;
@@ -340,20 +403,39 @@ __global__ __launch_bounds__(64 * RW) __attribute__((amdgpu_waves_per_eu(RW))) v
   // Â[r, j] = exp2(s_rj * sl2 - m_r) / (l_r * b') = exp2(s_rj * sl2 - m_r - log2(l_r * b')).
   // Lane (lr, lh) holds key lr of the tile for the 16 rows rv(v) = 32 w + 8 (v / 4) + 4 lh
   // + v % 4.
-  // (the 16 row statistics are loaded unconditionally, rows past b' clamped, so that the
-  // loads are in flight together)
+  // The row of each of the first ROWS threads first (its chunks merged here when there are
+  // few), then, through LDS, the 16 rows of the lane's weights.
+  static_assert(NT >= ROWS && LPITCH * LPAD >= 1, "a thread per row");
+  float *row_rm = acc_s;
+  if (tid < ROWS) {
+    float v = 0.f;
+    if (tid < bp) {
+      float2 st;
+      if (a.merge_inline) {
+        st = make_float2(-INFINITY, 0.f);
+        const float2 *cs = a.chunk_stats + ((int64_t)a.st.ch_off[s] * a.hq + h) * a.block + tid;
+        const int nc = a.st.ch_off[s + 1] - a.st.ch_off[s];
+        const int64_t step = (int64_t)a.hq * a.block;
+        for (int i = 0; i < nc; i += 8) {
+          float2 x[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            x[u] = i + u < nc ? cs[(i + u) * step] : make_float2(-INFINITY, 0.f);
+#pragma unroll
+          for (int u = 0; u < 8; ++u) st = merge_stats(st, x[u]);
+        }
+      } else {
+        st = a.row_stats[((int64_t)s * a.hq + h) * a.block + tid];
+      }
+      v = st.x + __builtin_amdgcn_logf(st.y * (float)bp);
+    }
+    row_rm[tid] = v;
+  }
+  __syncthreads();
   float rm[16];
-  float2 rst[16];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int rv = 32 * w + 8 * (v >> 2) + 4 * lh + (v & 3);
-    rst[v] = a.row_stats[((int64_t)s * a.hq + h) * a.block + min(rv, bp - 1)];
-  }
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int rv = 32 * w + 8 * (v >> 2) + 4 * lh + (v & 3);
-    rm[v] = rv < bp ? rst[v].x + __builtin_amdgcn_logf(rst[v].y * (float)bp) : 0.f;
-  }
+  for (int v = 0; v < 16; ++v) rm[v] = row_rm[32 * w + 8 * (v >> 2) + 4 * lh + (v & 3)];
+  __syncthreads();
   bf16x8 qf[D / 16];
   load_qhat<D>(a, tok0, n, h, r, lh, qf);
   for (int i = tid; i < a.st.ch_len; i += NT) acc_s[i] = 0.f;
@@ -440,54 +522,18 @@ __global__ __launch_bounds__(64 * RW) __attribute__((amdgpu_waves_per_eu(RW))) v
   }
 }
 
-// ---------------------------------------------------------------- block pooling
-
-// out[(blk) * H + head][d] = mean over the block's tokens of x[token][head][d].
-// Launched with grid (NB, H); heads whose pattern differs from `only_pattern` are
-// skipped when `pattern` is non-null.
-template <int D>
-__global__ __launch_bounds__(kThreads) void pool_blocks(SeqTable st, const uint16_t *x, int H,
-                                                        int block, float *out,
-                                                        const uint8_t *pattern, int hq,
-                                                        int only_pattern) {
-  constexpr int CH = D / 8;              // 16-byte chunks per row
-  constexpr int PH = kThreads / CH;      // token phases
-  __shared__ float part[PH][D];
-  const int blk = blockIdx.x, head = blockIdx.y;
-  const int s = seq_of_block(st, blk);
-  if (pattern && pattern[s * hq + head] != only_pattern) return;
-  const int tok0 = st.cu[s];
-  const int n = st.cu[s + 1] - tok0;
-  const int J = blk - st.nb_off[s];
-  const int t0 = J * block;
-  const int cntk = min(block, n - t0);
-  const int tid = threadIdx.x, ch = tid % CH, ph = tid / CH;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int t = ph; t < cntk; t += PH) {
-    const uint4 v = *reinterpret_cast<const uint4 *>(x + ((int64_t)(tok0 + t0 + t) * H + head) * D +
-                                                     ch * 8);
-    const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc[2 * i] += __uint_as_float(wv[i] << 16);
-      acc[2 * i + 1] += __uint_as_float(wv[i] & 0xFFFF0000u);
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) part[ph][ch * 8 + i] = acc[i];
-  __syncthreads();
-  if (tid < D) {
-    float sum = 0.f;
-    for (int p = 0; p < PH; ++p) sum += part[p][tid];
-    out[((int64_t)blk * H + head) * D + tid] = sum / (float)cntk;
-  }
-}
-
 }  // namespace
 
-hipError_t launch_rep_scores(const SelectArgs &a, hipStream_t stream) {
+hipError_t launch_rep_scores(const SelectArgs &args, hipStream_t stream) {
+  SelectArgs a = args;
   const int ch_total = a.st.ch_off[a.st.n_seq];
-  dim3 grid(ch_total, a.hq);
+  // rows of few chunks are merged by the line pass itself
+  int most = 0;
+  for (int s = 0; s < a.st.n_seq; ++s) most = std::max(most, a.st.ch_off[s + 1] - a.st.ch_off[s]);
+  a.merge_inline = most <= kMergeInline;
+  // short layers: every head's Q̄ comes from workgroups of the line pass (which leaves CUs
+  // free), before it is known which heads need it
+  const dim3 grid(ch_total + (a.pool_inline ? a.nb_total : 0), a.hq);
   // 4 (or 2) query heads of one KV group per workgroup when the group size allows
   const int G = a.hq / a.hkv;
   int hg = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
@@ -513,8 +559,9 @@ hipError_t launch_rep_scores(const SelectArgs &a, hipStream_t stream) {
     if (rw == 4) stats(I64{}, I4{});
     else stats(I64{}, I2{});
   }
-  hipLaunchKernelGGL(rep_stats_combine, dim3(a.st.n_seq, a.hq, (a.block + 3) / 4), dim3(256), 0,
-                     stream, a);
+  if (!a.merge_inline)
+    hipLaunchKernelGGL(rep_stats_combine, dim3(a.st.n_seq, a.hq, (a.block + 3) / 4), dim3(256), 0,
+                       stream, a);
   if (a.d == 128) {
     if (rw == 4) hipLaunchKernelGGL((rep_lines<128, 4>), grid, dim3(64 * rw), 0, stream, a);
     else hipLaunchKernelGGL((rep_lines<128, 2>), grid, dim3(64 * rw), 0, stream, a);
@@ -526,6 +573,7 @@ hipError_t launch_rep_scores(const SelectArgs &a, hipStream_t stream) {
 }
 
 hipError_t launch_pool_q_query_aware(const SelectArgs &a, hipStream_t stream) {
+  if (a.pool_inline) return hipSuccess;
   if (a.d == 128)
     hipLaunchKernelGGL(pool_blocks<128>, dim3(a.nb_total, a.hq), dim3(kThreads), 0, stream, a.st,
                        a.q, a.hq, a.block, a.qbar, (const uint8_t *)a.pattern, a.hq,

@@ -263,22 +263,23 @@ __global__ __launch_bounds__(1024) void sel_tie(SelectArgs a) {
   }
 }
 
-// Short problems: every selection problem of the call in one 1024-thread workgroup, the
+// Short problems: every selection problem of the call in one workgroup of NT threads, the
 // three radix passes through an LDS histogram and the lowest-id tie break in the same
 // launch -- one launch instead of the seven above, the same threshold key, counts and
 // tie cut (every sum is an exact integer, so the result does not depend on the path).
-// A thread holds its E scores (units tid + 1024 e) in registers over the passes.  The LDS
+// A thread holds its E scores (units tid + NT e) in registers over the passes.  The LDS
 // atomics bound it (many scores share a bucket), so the histogram holds masses only: units
 // of the threshold key all carry that key's own mass, and the units above it are counted
 // once at the end (32 heads: 15.3 -> 11.7 us at 4k tokens, 35.5 -> 26.4 at 16k).
 constexpr int kSmallUnits = 16384;    // largest problem (units) taken by sel_small
 
-template <int E>
-__global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
+template <int NT, int E>
+__global__ __launch_bounds__(NT) void sel_small(SelectArgs a) {
   __shared__ unsigned long long mass[kHistBuckets];
-  __shared__ unsigned long long wmass[16];
+  constexpr int NW = NT / 64, BPT = kHistBuckets / NT;   // waves, buckets per thread
+  __shared__ unsigned long long wmass[NW];
   __shared__ unsigned long long s_run;
-  __shared__ uint32_t s_digit, wcount[16];
+  __shared__ uint32_t s_digit, wcount[NW];
   __shared__ int found;
   const int p = blockIdx.x, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   SelState S = a.sel[p];
@@ -286,17 +287,17 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
   const Problem pr = problem_of(a, p);
   float xs[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) xs[e] = tid + 1024 * e < S.n ? pr.scores[tid + 1024 * e] : 0.f;
-  const int top = kHistBuckets - 2 * tid; // thread t owns buckets [top - 2, top): thread
-                                          // order is descending key order
+  for (int e = 0; e < E; ++e) xs[e] = tid + NT * e < S.n ? pr.scores[tid + NT * e] : 0.f;
+  // thread t owns buckets [top - BPT, top): thread order is descending key order
+  const int top = kHistBuckets - BPT * tid;
 #pragma unroll 1
   for (int pass = 0; pass < 3; ++pass) {
     const int shift = pass == 0 ? 21 : (pass == 1 ? 10 : 0);
     const uint32_t dmask = pass == 2 ? 1023u : 2047u;
     // key bits that the earlier passes fixed
     const uint32_t fixed = pass == 0 ? 0u : (pass == 1 ? ~0u << 21 : ~0u << 10);
-    mass[tid] = 0ull;
-    mass[tid + 1024] = 0ull;
+#pragma unroll
+    for (int b = 0; b < BPT; ++b) mass[tid + NT * b] = 0ull;
     __syncthreads();
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -306,11 +307,15 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
         atomicAdd(&mass[(key >> shift) & dmask], fx);
     }
     __syncthreads();
-    const unsigned long long bm[2] = {mass[top - 1], mass[top - 2]};
-    const unsigned long long lm = bm[0] + bm[1];
+    unsigned long long bm[BPT], lm = 0ull;
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) {
+      bm[i] = mass[top - 1 - i];
+      lm += bm[i];
+    }
     unsigned long long im = lm, total;
     uint32_t ic = 0u, total_c;
-    block_incl_scan<16>(im, ic, wmass, wcount, total, total_c);
+    block_incl_scan<NW>(im, ic, wmass, wcount, total, total_c);
     if (pass == 0) {
       S.total = total;
       if (total == 0ull) {
@@ -332,7 +337,7 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
     }
     unsigned long long run = S.mass_above + im - lm;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < BPT; ++i) {
       if (run < S.thr && run + bm[i] >= S.thr) {   // exactly one bucket of all threads
         s_digit = (uint32_t)(top - 1 - i);
         s_run = run;
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
 #pragma unroll
   for (int e = 0; e < E; ++e) {
     const uint32_t key = __float_as_uint(xs[e]);
-    const bool in = tid + 1024 * e < S.n;
+    const bool in = tid + NT * e < S.n;
     c += (in && key > S.key ? 1u << 16 : 0u) + (in && key == S.key ? 1u : 0u);
   }
   // (a sum of at most 2^16 units per half does not carry over: S.n <= 2^14)
@@ -363,7 +368,7 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
   __syncthreads();
   c = 0u;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) c += wcount[k];
+  for (int k = 0; k < NW; ++k) c += wcount[k];
   S.cnt_above = c >> 16;
   S.n_eq = c & 0xFFFFu;
   S.k = (int32_t)(S.cnt_above + S.need_eq);
@@ -373,15 +378,15 @@ __global__ __launch_bounds__(1024) void sel_small(SelectArgs a) {
     uint32_t running = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      if (1024 * e >= S.n) break;
-      const int i = 1024 * e + tid;
+      if (NT * e >= S.n) break;
+      const int i = NT * e + tid;
       const bool f = i < S.n && __float_as_uint(xs[e]) == S.key;
       const unsigned long long bal = __ballot(f);
       __syncthreads();                    // the last reads of wcount and found are done
       if (lane == 0) wcount[w] = (uint32_t)__popcll(bal);
       __syncthreads();
       uint32_t before = 0, chunk = 0;
-      for (int k = 0; k < 16; ++k) {
+      for (int k = 0; k < NW; ++k) {
         if (k < w) before += wcount[k];
         chunk += wcount[k];
       }
@@ -467,6 +472,11 @@ __device__ __forceinline__ void mark_blocks(const SelectArgs &a, int s, int h, c
 // scores: sequences of up to kMarkInline tokens, and block-pooled lines of any length.
 constexpr int kMarkSlice = 8192;
 constexpr int kMarkInline = 8192;
+
+// Layers whose Q is at most this large are pooled by the line pass, all heads of it: at 0.5 MB
+// (two heads, 2k tokens) selection 49.2 -> 47.8 us, at 8 MB (32 heads, 1000 tokens) 63.4 ->
+// 59.2; at 32 MB (4k tokens) the line pass's own workgroups wait for it: 78.7 -> 81.1.
+constexpr int64_t kPoolInlineBytes = 10 << 20;
 
 __global__ __launch_bounds__(256) void vs_marks(SelectArgs a) {
   const int s = blockIdx.x / a.hq, h = blockIdx.x % a.hq;
@@ -945,6 +955,7 @@ hipError_t launch_select_pipeline(const SelectArgs &args, hipStream_t stream) {
   }
   a.marks_inline = a.vs_granularity == 1 || max_n <= kMarkInline;
   a.small = max_units <= kSmallUnits;
+  a.pool_inline = (int64_t)a.total_tokens * a.hq * a.d * 2 <= kPoolInlineBytes;
   hipError_t e;
   if ((e = launch_rep_scores(a, stream)) != hipSuccess) return e;
   if ((e = launch_pattern_search(a, stream)) != hipSuccess) return e;
@@ -955,10 +966,14 @@ hipError_t launch_select_pipeline(const SelectArgs &args, hipStream_t stream) {
   if (a.vs_granularity == 1)
     hipLaunchKernelGGL(pool_lines, dim3((a.nb_total + 3) / 4, a.hq), dim3(256), 0, stream, a);
   if (a.small) {
-    if (max_units <= 4096)
-      hipLaunchKernelGGL(sel_small<4>, dim3(problems), dim3(1024), 0, stream, a);
+    // many small problems: eight workgroups of 256 threads a CU instead of two of 1024
+    // (64 sequences of 8 heads: 39.4 -> 19.3 us)
+    if (max_units <= 4096 && problems > 512)
+      hipLaunchKernelGGL((sel_small<256, 16>), dim3(problems), dim3(256), 0, stream, a);
+    else if (max_units <= 4096)
+      hipLaunchKernelGGL((sel_small<1024, 4>), dim3(problems), dim3(1024), 0, stream, a);
     else
-      hipLaunchKernelGGL(sel_small<16>, dim3(problems), dim3(1024), 0, stream, a);
+      hipLaunchKernelGGL((sel_small<1024, 16>), dim3(problems), dim3(1024), 0, stream, a);
   } else {
     hipLaunchKernelGGL(sel_hist<0>, dim3(slices, problems), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sel_scan<0>, dim3(problems), dim3(256), 0, stream, a);

@@ -1,4 +1,6 @@
-"""Selection at the sizes where its launches change: whole rows of the pooled map in one tile
+"""Selection at the sizes where its launches change: chunk statistics merged by the line pass
+(up to 16 chunks of 256 keys), workgroups of 256 threads (up to 16 blocks), Q pooled by the
+line pass (up to 10 MB), whole rows of the pooled map in one tile
 (up to 128 key blocks), the pattern search in one workgroup (up to 128), line marks made by
 the list conversion (up to 8192 tokens), every selection problem in one workgroup (up to
 16384 units), against the oracle."""
@@ -22,7 +24,12 @@ CASES = [
     ((11521,), 64, 0),           # 181 blocks: 16471 units
     ((16384, 130), 128, 0),      # 128 blocks, 16384 lines
     ((16385,), 128, 0),          # 129 blocks, 16385 lines
-    ((4096, 4097), 128, 0),      # four and five scores per thread
+    ((4096, 4097), 128, 0),      # four and five scores per thread, 17 chunks
+    ((4096, 1, 300), 128, 0),    # 16 chunks
+    ((2048, 5), 128, 0),         # 16 blocks
+    ((2049, 129), 128, 0),       # 17 blocks
+    ((20480,), 128, 0),          # Q of 10 MB
+    ((20481,), 128, 0),          # and one token more
     ((16385, 65), 128, 1),       # block-pooled lines of a long sequence
 ]
 
