@@ -190,6 +190,7 @@ size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, cha
       a->unit_cap = (int)cap;
       a->extra = (int)extra;
       a->all = extra == most;
+      a->resident = cap * hkv <= slots;
     }
     return o3 + part * n_slot;
   };

@@ -1102,13 +1102,16 @@ __device__ __forceinline__ void split_group_items(const SeqTable &st, const int3
   }
   __syncthreads();
   const int n_u = n_unit;
-  switch (np / kSortThreads) {
-    case 1: sort_keys<1>(key, key, n_u); break;
-    case 2: sort_keys<2>(key, key, n_u); break;
-    default: sort_keys<4>(key, key, n_u); break;
+  // (all units resident at once: their order does not matter)
+  if (!sp.resident) {
+    switch (np / kSortThreads) {
+      case 1: sort_keys<1>(key, key, n_u); break;
+      case 2: sort_keys<2>(key, key, n_u); break;
+      default: sort_keys<4>(key, key, n_u); break;
+    }
   }
   for (int t = threadIdx.x; t < cap; t += blockDim.x) {
-    const int u = t < n_u ? (int)(key[t] & 0x3FFF) : 0;
+    const int u = t >= n_u ? 0 : sp.resident ? t : (int)(key[t] & 0x3FFF);
     sp.units[(int64_t)g * cap + t] = t < n_u ? rec[u] : make_int4(0, -1, -1, -1);
     sp.segs[(int64_t)g * cap + t] = seg[u];
   }
