@@ -47,8 +47,9 @@ struct SelectArgs {
   // set by the launcher: every selection problem in one workgroup (no histograms), and the
   // line marks made by convert_tiles itself (no vs_marks)
   int32_t small, marks_inline;
-  // set by the launchers: the line pass merges the chunk statistics, and pools Q
-  int32_t merge_inline, pool_inline;
+  // set by the launchers: the line pass merges the chunk statistics, pools Q, and the parts
+  // it cuts a score chunk into
+  int32_t merge_inline, pool_inline, line_parts;
   // workspace
   float2 *chunk_stats;     // [ch_total][Hq][block] (max, sum) in log2 units
   float2 *row_stats;       // [n_seq][Hq][block]
