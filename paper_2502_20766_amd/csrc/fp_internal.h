@@ -80,16 +80,16 @@ struct SelState {
   unsigned long long total;       // fixed-point mass of all units
   unsigned long long thr;         // ceil(gamma * total)
   unsigned long long mass_above;  // mass of keys above the current digit range
+  unsigned long long ticket;      // slices of the radix pass that are done, and (in the upper
+                                  // 32 bits) the units that they counted above its range
   uint32_t cnt_above;             // number of keys above the current digit range
   uint32_t prefix;                // key bits fixed so far
   uint32_t key;                   // final threshold key
   uint32_t need_eq;               // units with key == `key` to take (lowest ids first)
-  uint32_t n_eq;                  // units with key == `key`
   int32_t idcut;                  // last id taken among key == `key`
   int32_t k;                      // units selected
   int32_t mode;                   // 0 active, 1 take all, 2 inactive (other pattern)
   int32_t n;                      // number of units
-  int32_t pad;
 };
 
 // The split grid is taken for at most this many tenths of a row per resident workgroup.

@@ -93,87 +93,114 @@ __device__ __forceinline__ bool is_selected(const SelState &S, float x, int id) 
   return key > S.key || (key == S.key && id <= S.idcut);
 }
 
+// One radix pass over every problem: grid (slices of kSlice units, problems), 256 threads.
+// A workgroup adds its slice's masses per digit to the problem's histogram; the last one of a
+// problem to do so (a ticket in the problem's state) finds the digit whose bucket carries the
+// cumulative mass across the threshold.  Counts are not taken per digit: pass 2 counts the
+// units above its range in registers and the few units inside it by their last digit, which
+// halves the LDS atomics that bound pass 0.  The scan and the tie break had launches of their
+// own before: 51 us for the seven launches at 32 heads and 32k tokens (92 at 128k), 36 (78) for
+// these three.
+// The histograms and the ticket are shared between XCDs: device-scope atomics and loads, each
+// workgroup's additions waited for before its ticket.
 template <int PASS>
 __global__ __launch_bounds__(256) void sel_hist(SelectArgs a) {
-  __shared__ uint32_t cnt[kHistBuckets];
-  __shared__ unsigned long long mass[kHistBuckets];
-  const int p = blockIdx.y;
-  const SelState S = a.sel[p];
+  constexpr int NB = PASS == 2 ? 1024 : kHistBuckets;      // digits of this pass
+  constexpr int shift = PASS == 0 ? 21 : (PASS == 1 ? 10 : 0);
+  __shared__ unsigned long long mass[NB];
+  __shared__ uint32_t cnt[PASS == 2 ? NB : 1];
+  __shared__ unsigned long long wmass[4];
+  __shared__ uint32_t wcnt[16], s_need;
+  __shared__ int s_last, found;
+  const int p = blockIdx.y, tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  SelState S = a.sel[p];
   if (S.mode != 0) return;
   const int start = blockIdx.x * kSlice;
   if (start >= S.n) return;
   const Problem pr = problem_of(a, p);
-  for (int b = threadIdx.x; b < kHistBuckets; b += blockDim.x) {
-    cnt[b] = 0u;
+  for (int b = tid; b < NB; b += 256) {
     mass[b] = 0ull;
+    if constexpr (PASS == 2) cnt[b] = 0u;
   }
   __syncthreads();
-  constexpr int shift = PASS == 0 ? 21 : (PASS == 1 ? 10 : 0);
-  constexpr uint32_t dmask = PASS == 2 ? 1023u : 2047u;
   const int end = min(start + kSlice, S.n);
-  const int nt = blockDim.x;
+  uint32_t above = 0u;                     // units above the range of the earlier digits
   // four scores per thread are loaded before their histogram updates
-  for (int base = start + threadIdx.x; base < end; base += 4 * nt) {
+  for (int base = start + tid; base < end; base += 4 * 256) {
     float xs[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = base + u * nt;
-      xs[u] = i < end ? pr.scores[i] : 0.f;
-    }
+    for (int u = 0; u < 4; ++u) xs[u] = base + u * 256 < end ? pr.scores[base + u * 256] : 0.f;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (base + u * nt >= end) break;
+      if (base + u * 256 >= end) break;
       const float x = xs[u];
       const uint32_t key = __float_as_uint(x);
       bool match = true;
       if (PASS == 1) match = (key >> 21) == (S.prefix >> 21);
-      if (PASS == 2) match = (key >> 10) == (S.prefix >> 10);
+      if (PASS == 2) {
+        match = (key >> 10) == (S.prefix >> 10);
+        above += (key >> 10) > (S.prefix >> 10);
+      }
+      const uint32_t dg = (key >> shift) & (uint32_t)(NB - 1);
       if (match) {
-        const uint32_t dg = (key >> shift) & dmask;
-        atomicAdd(&cnt[dg], 1u);
-        atomicAdd(&mass[dg], to_fx(x));
+        const unsigned long long fx = to_fx(x);
+        if (fx != 0ull) atomicAdd(&mass[dg], fx);
+        if constexpr (PASS == 2) atomicAdd(&cnt[dg], 1u);
       }
     }
   }
-  __syncthreads();
-  for (int b = threadIdx.x; b < kHistBuckets; b += blockDim.x) {
-    if (cnt[b]) {
-      atomicAdd(&a.hist_cnt[(int64_t)p * kHistBuckets + b], cnt[b]);
-      atomicAdd(&a.hist_mass[(int64_t)p * kHistBuckets + b], mass[b]);
-    }
+  if constexpr (PASS == 2) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) above += __shfl_xor(above, off);
+    if (lane == 0) wcnt[w] = above;
   }
-}
-
-// Find the digit whose bucket carries the cumulative mass across the threshold.  Thread t
-// owns buckets [2048 - 8(t+1), 2048 - 8t), so thread order is descending key order.
-template <int PASS>
-__global__ __launch_bounds__(256) void sel_scan(SelectArgs a) {
-  __shared__ unsigned long long wmass[4];
-  __shared__ uint32_t wcnt[4];
-  const int p = blockIdx.x, tid = threadIdx.x;
-  SelState S = a.sel[p];
-  if (S.mode != 0) return;
+  __syncthreads();
   unsigned long long *hm = a.hist_mass + (int64_t)p * kHistBuckets;
   uint32_t *hc = a.hist_cnt + (int64_t)p * kHistBuckets;
-  const int top = kHistBuckets - 8 * tid;   // exclusive upper bucket
-  unsigned long long bm[8];
-  uint32_t bc[8];
-  unsigned long long lm = 0;
-  uint32_t lc = 0;
+  for (int b = tid; b < NB; b += 256) {
+    if (mass[b]) atomicAdd(&hm[b], mass[b]);
+    if constexpr (PASS == 2)
+      if (cnt[b]) atomicAdd(&hc[b], cnt[b]);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    const uint32_t slices = (S.n + kSlice - 1) / kSlice;
+    const unsigned long long mine =
+        PASS == 2 ? (unsigned long long)(wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3]) << 32 : 0ull;
+    const unsigned long long done = __hip_atomic_fetch_add(&a.sel[p].ticket, mine + 1,
+                                                           __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT) + mine;
+    s_last = (uint32_t)done == slices - 1;
+    s_need = (uint32_t)(done >> 32);
+  }
+  __syncthreads();
+  if (!s_last) return;
+  S.cnt_above = s_need;                    // (every workgroup's count, in the last one)
+  // thread t owns buckets [NB - BPT (t + 1), NB - BPT t): thread order is descending key order
+  constexpr int BPT = NB / 256;
+  const int top = NB - BPT * tid;
+  unsigned long long bm[BPT], lm = 0ull;
+  uint32_t bc[BPT], lc = 0u;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    bm[i] = hm[top - 1 - i];
-    bc[i] = hc[top - 1 - i];
+  for (int i = 0; i < BPT; ++i) {
+    bm[i] = __hip_atomic_load(&hm[top - 1 - i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bc[i] = 0u;
+    if constexpr (PASS == 2)
+      bc[i] = __hip_atomic_load(&hc[top - 1 - i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     lm += bm[i];
     lc += bc[i];
   }
-  unsigned long long im = lm, s_total;
-  uint32_t ic = lc, s_count;
-  block_incl_scan<4>(im, ic, wmass, wcnt, s_total, s_count);
-  const unsigned long long excl_m = im - lm;
-  const uint32_t excl_c = ic - lc;
+  // (cleared for the next pass)
+  if constexpr (PASS < 2) {
+#pragma unroll
+    for (int i = 0; i < BPT; ++i) hm[top - 1 - i] = 0ull;
+  }
+  unsigned long long im = lm, total;
+  uint32_t ic = lc, count;
+  block_incl_scan<4>(im, ic, wmass, wcnt, total, count);
+  S.ticket = 0ull;
   if (PASS == 0) {
-    const unsigned long long total = s_total;
     S.total = total;
     if (total == 0ull) {
       S.mode = 1;
@@ -184,88 +211,88 @@ __global__ __launch_bounds__(256) void sel_scan(SelectArgs a) {
       if (thr > total) S.mode = 1;    // never reached: take every unit
       S.thr = thr;
     }
-    if (S.mode == 1) {
+    if (S.mode == 1) {                // the same in every thread
       S.key = 0u;
       S.idcut = 0x7FFFFFFF;
       S.k = S.n;
+      if (tid == 0) a.sel[p] = S;
+      return;
     }
   }
+  if (tid == 0) s_need = 0u;
   __syncthreads();
-  // all threads zero their buckets for the next pass once everyone has read them
-  for (int i = 0; i < 8; ++i) {
-    hm[top - 1 - i] = 0ull;
-    hc[top - 1 - i] = 0u;
-  }
-  if (S.mode == 1) {
-    if (tid == 0) a.sel[p] = S;
-    return;
-  }
-  constexpr int shift = PASS == 0 ? 21 : (PASS == 1 ? 10 : 0);
-  unsigned long long run = S.mass_above + excl_m;
-  uint32_t runc = S.cnt_above + excl_c;
+  unsigned long long run = S.mass_above + im - lm;
+  uint32_t runc = S.cnt_above + ic - lc;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (run < S.thr && run + bm[i] >= S.thr) {
-      const uint32_t digit = (uint32_t)(top - 1 - i);
-      S.prefix |= digit << shift;
-      S.mass_above = run;
-      S.cnt_above = runc;
-      if (PASS == 2) {
-        S.key = S.prefix;
-        S.n_eq = bc[i];
+  for (int i = 0; i < BPT; ++i) {
+    if (run < S.thr && run + bm[i] >= S.thr) {     // exactly one bucket of all threads
+      SelState T = S;
+      T.prefix |= (uint32_t)(top - 1 - i) << shift;
+      T.mass_above = run;
+      if constexpr (PASS == 2) {
+        T.cnt_above = runc;
+        T.key = T.prefix;
         const unsigned long long f = bm[i] / bc[i];   // equal keys carry equal mass
-        const unsigned long long need = (S.thr - run + f - 1) / f;
-        S.need_eq = (uint32_t)need;
-        S.k = (int32_t)(runc + need);
-        S.idcut = (need >= bc[i]) ? 0x7FFFFFFF : -1;
+        const unsigned long long need = (T.thr - run + f - 1) / f;
+        T.need_eq = (uint32_t)need;
+        T.k = (int32_t)(runc + need);
+        T.idcut = 0x7FFFFFFF;
+        if (need < bc[i]) {
+          s_need = (uint32_t)need;
+          wcnt[0] = T.key;
+        }
       }
-      a.sel[p] = S;
+      a.sel[p] = T;
     }
     run += bm[i];
     runc += bc[i];
   }
-}
-
-// Lowest-id tie break: find the id of the need_eq-th unit (in id order) whose key equals
-// the threshold key.  Only runs when some but not all of those units are taken.
-__global__ __launch_bounds__(1024) void sel_tie(SelectArgs a) {
-  __shared__ uint32_t wcount[16];
-  __shared__ int found;
-  const int p = blockIdx.x;
-  SelState S = a.sel[p];
-  if (S.mode != 0 || S.idcut != -1) return;
-  const Problem pr = problem_of(a, p);
-  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  uint32_t running = 0;
-  if (tid == 0) found = -1;
-  __syncthreads();
-  for (int base = 0; base < S.n; base += 1024) {
-    const int i = base + tid;
-    const bool f = i < S.n && __float_as_uint(pr.scores[i]) == S.key;
-    const unsigned long long bal = __ballot(f);
-    if (lane == 0) wcount[w] = (uint32_t)__popcll(bal);
+  if constexpr (PASS == 2) {
+    // lowest-id tie break, when some but not all units of the key are taken: the id of the
+    // need-th unit (in id order) whose key is the threshold key
     __syncthreads();
-    uint32_t before = 0, chunk = 0;
-    for (int k = 0; k < 16; ++k) {
-      if (k < w) before += wcount[k];
-      chunk += wcount[k];
+    const uint32_t need = s_need, tkey = wcnt[0];
+    if (need == 0u) return;
+    uint32_t running = 0;
+    if (tid == 0) found = -1;
+    for (int base = 0; base < S.n; base += 1024) {
+      bool f[4];
+      unsigned long long bal[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int i = base + 256 * u + tid;
+        f[u] = i < S.n && __float_as_uint(pr.scores[i]) == tkey;
+        bal[u] = __ballot(f[u]);
+      }
+      __syncthreads();                     // the last reads of wcnt and found are done
+      if (lane < 4) wcnt[4 * lane + w] = (uint32_t)__popcll(lane == 0   ? bal[0]
+                                                            : lane == 1 ? bal[1]
+                                                            : lane == 2 ? bal[2]
+                                                                        : bal[3]);
+      __syncthreads();
+      uint32_t before = running;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          if (k == w) {
+            const uint32_t rank = before + (uint32_t)__popcll(bal[u] & __lanemask_lt());
+            if (f[u] && rank + 1 == need) found = base + 256 * u + tid;
+          }
+          before += wcnt[4 * u + k];
+        }
+      }
+      running = before;
+      if (running >= need) break;          // the same in every thread
     }
-    const uint32_t rank = running + before + (uint32_t)__popcll(bal & __lanemask_lt());
-    if (f && rank + 1 == S.need_eq) found = i;
     __syncthreads();
-    if (found >= 0) break;
-    running += chunk;
-    __syncthreads();
-  }
-  if (tid == 0) {
-    S.idcut = found;
-    a.sel[p] = S;
+    if (tid == 0) a.sel[p].idcut = found;
   }
 }
 
 // Short problems: every selection problem of the call in one workgroup of NT threads, the
 // three radix passes through an LDS histogram and the lowest-id tie break in the same
-// launch -- one launch instead of the seven above, the same threshold key, counts and
+// launch -- one launch instead of the three above, the same threshold key, counts and
 // tie cut (every sum is an exact integer, so the result does not depend on the path).
 // A thread holds its E scores (units tid + NT e) in registers over the passes.  The LDS
 // atomics bound it (many scores share a bucket), so the histogram holds masses only: units
@@ -370,11 +397,11 @@ __global__ __launch_bounds__(NT) void sel_small(SelectArgs a) {
 #pragma unroll
   for (int k = 0; k < NW; ++k) c += wcount[k];
   S.cnt_above = c >> 16;
-  S.n_eq = c & 0xFFFFu;
+  const uint32_t n_eq = c & 0xFFFFu;
   S.k = (int32_t)(S.cnt_above + S.need_eq);
   S.idcut = 0x7FFFFFFF;
-  // lowest-id tie break (as sel_tie), when some but not all units of the key are taken
-  if (S.need_eq < S.n_eq) {
+  // lowest-id tie break, when some but not all units of the key are taken
+  if (S.need_eq < n_eq) {
     uint32_t running = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -587,6 +614,38 @@ __global__ __launch_bounds__(1024) void convert_tiles(SelectArgs a) {
             jmin = top - 63;
           }
         }
+      } else if (I < 256) {
+        // rows of up to 256 blocks: the unselected blocks' scores stay in registers (-1 for
+        // the others), one butterfly per added block
+        float xs[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int J = 64 * u + lane;
+          xs[u] = J <= I ? flat[tri_row + J] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int J = 64 * u + lane;
+          if (J > I || J == 0 || J == I || is_selected(S0, xs[u], (int)(tri_row + J))) xs[u] = -1.f;
+        }
+        for (; n_added < need; ++n_added) {
+          float best = -1.f;
+          int bj = 0x7FFFFFFF;
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (xs[u] > best) { best = xs[u]; bj = 64 * u + lane; }
+          for (int off = 32; off > 0; off >>= 1) {
+            const float ob = __shfl_xor(best, off);
+            const int oj = __shfl_xor(bj, off);
+            if (ob > best || (ob == best && oj < bj)) { best = ob; bj = oj; }
+          }
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+            if (bj == 64 * u + lane) xs[u] = -1.f;
+          if (lane == 0) added[w][n_added] = bj;
+        }
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
       } else {
         for (; n_added < need; ++n_added) {
           float best = -1.f;
@@ -976,12 +1035,8 @@ hipError_t launch_select_pipeline(const SelectArgs &args, hipStream_t stream) {
       hipLaunchKernelGGL((sel_small<1024, 16>), dim3(problems), dim3(1024), 0, stream, a);
   } else {
     hipLaunchKernelGGL(sel_hist<0>, dim3(slices, problems), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(sel_scan<0>, dim3(problems), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sel_hist<1>, dim3(slices, problems), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(sel_scan<1>, dim3(problems), dim3(256), 0, stream, a);
     hipLaunchKernelGGL(sel_hist<2>, dim3(slices, problems), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(sel_scan<2>, dim3(problems), dim3(256), 0, stream, a);
-    hipLaunchKernelGGL(sel_tie, dim3(problems), dim3(1024), 0, stream, a);
   }
   {
     if (!a.marks_inline)

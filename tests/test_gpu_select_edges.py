@@ -56,3 +56,28 @@ def test_selection_at_the_edges_of_its_launches(case):
     assert_relaxations_bounded(st)
     mx, mean = compare_outputs(layer, g["o"], g["masks"], rows_per_head=3)
     assert mx <= O_MAX_ABS and mean <= O_MEAN_ABS
+
+
+@pytest.mark.parametrize("n", [16384, 16385])
+def test_ties_at_the_threshold_take_the_lowest_ids(n):
+    """Q = 0 makes every score of a pooled row the same number (1 / (I + 1), in float32 as in
+    float64): the cut falls inside a run of equal units, which the lowest ids fill -- with every
+    problem in one workgroup, and with the radix passes over slices."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import numpy as np
+    import oracle
+    import paper_2502_20766_amd as fpx
+    log(f"[select ties] {n}")
+    spec = BASE.with_seqlens((n,), f"ties-{n}").with_params(hq=2, hkv=1, head_kinds=("vs", "qa"),
+                                                            min_budget=1)
+    layer = synth.make_layer(spec)
+    layer.q[:] = 0.0
+    q, k, _ = to_device(layer)
+    idx = fpx.select(q, k, layer.cu_seqlens, spec.gamma, spec.tau, spec.min_budget,
+                     force_pattern=0)
+    masks = fpx.masks_from_indices(idx)
+    ref = oracle.select(layer.q, layer.k, layer.cu_seqlens, spec.block, spec.gamma, spec.tau,
+                        spec.min_budget, force_pattern=0)
+    for h in range(2):
+        np.testing.assert_array_equal(masks[(0, h)], ref[0][h]["mask"])
