@@ -1042,8 +1042,8 @@ __device__ __forceinline__ void sort_group_items(const SeqTable &st, const int32
 
 // The split grid's units of KV group g: its items, those listing more than L blocks cut
 // into segments of about equal length, in the order of the keys above (a segment's key
-// holds its own length and first blocks).  L is the group's share of blocks per resident
-// workgroup, and at least kSegBlocks; with L = W / extra (W the group's listed blocks) the
+// holds its own length and first blocks).  L is the group's blocks over its share of the
+// resident workgroups, and at least kSegBlocks; with L = W / extra (W the group's listed blocks) the
 // cuts add at most `extra` units and fill at most 2 * extra partial slots.  Unit and slot
 // numbers are handed out as the threads come: they decide the order among equals and where
 // a partial result lies, not its value.
@@ -1102,8 +1102,11 @@ __device__ __forceinline__ void split_group_items(const SeqTable &st, const int3
   }
   __syncthreads();
   const int n_u = n_unit;
-  // (all units resident at once: their order does not matter)
-  if (!sp.resident) {
+  // units that are all resident at once (were every group this group's size) need no order:
+  // two heads at 2k tokens, preparation 12.5 -> 8.7 us; 8 heads at 4k on own lists, attention
+  // 44.7 -> 39.6
+  const bool sorted = n_u * hkv > sp.slots;
+  if (sorted) {
     switch (np / kSortThreads) {
       case 1: sort_keys<1>(key, key, n_u); break;
       case 2: sort_keys<2>(key, key, n_u); break;
@@ -1111,7 +1114,7 @@ __device__ __forceinline__ void split_group_items(const SeqTable &st, const int3
     }
   }
   for (int t = threadIdx.x; t < cap; t += blockDim.x) {
-    const int u = t >= n_u ? 0 : sp.resident ? t : (int)(key[t] & 0x3FFF);
+    const int u = t >= n_u ? 0 : sorted ? (int)(key[t] & 0x3FFF) : t;
     sp.units[(int64_t)g * cap + t] = t < n_u ? rec[u] : make_int4(0, -1, -1, -1);
     sp.segs[(int64_t)g * cap + t] = seg[u];
   }

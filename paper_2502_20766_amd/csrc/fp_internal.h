@@ -115,7 +115,7 @@ struct SplitArgs {
   int32_t unit_cap;        // units per KV group, the unused last ones marked empty
   int32_t extra;           // units per KV group beyond its rows; 2 * extra slots
   int32_t all;             // `extra` covers every segment of kSegBlocks
-  int32_t resident;        // all units run at the same time
+  int32_t slots;           // resident workgroups of the chip
 };
 
 struct AttnArgs {
