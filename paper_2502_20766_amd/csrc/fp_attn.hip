@@ -25,6 +25,14 @@
 // A persistent grid walks each KV group's (sequence, query head, query block) items in a
 // locality order (longest lists first in buckets, lists that start alike adjacent), every
 // group served by the same XCD(s), so that items running together share K/V tiles in L2.
+// Short problems run one workgroup per row, or per segment of a long row's list, instead.
+//
+// What bounds it: at two waves per SIMD (head dim 128) the matrix pipe is busy 61% of cycles
+// and the vector unit 44%, at the clock that the power limit leaves (1050 TFLOP/s on computed
+// tiles at 32 heads and 128k tokens); taking the weights first and checking their sum instead
+// of the row max (15 vector instructions fewer per stage) put that sum between the weights
+// and the P V product and was 2-4% slower; 32-key stages at three waves gained 1.5% there and
+// lost 1.5-40% on other sizes.
 #include <algorithm>
 #include <type_traits>
 
