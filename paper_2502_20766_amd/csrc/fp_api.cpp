@@ -181,7 +181,8 @@ size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, cha
   const int64_t part = (int64_t)block * (d + 4) * 4;   // O, then two floats per lane of a row
   auto layout = [&](int64_t extra, fp::SplitArgs *a) {
     const int64_t cap = n_g + extra, n_slot = 2 * extra * hkv;
-    const size_t o1 = align_up(16 * cap * hkv), o2 = o1 + align_up(16 * cap * hkv), o3 = o2 + align_up(8 * n_slot);
+    const size_t o1 = align_up(16 * cap * hkv), o2 = o1 + align_up(16 * cap * hkv),
+                 o3 = o2 + align_up(4 * n_slot);
     if (a) {
       a->units = (int4 *)room;
       a->segs = (int4 *)(room + o1);

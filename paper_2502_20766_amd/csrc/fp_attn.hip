@@ -367,10 +367,10 @@ __device__ __forceinline__ int stage_first_key(const Row &r, int J, int half) {
 //
 // With SPLIT (short problems, whose longest rows would otherwise end long after the others)
 // the grid holds one workgroup per unit instead: a unit is a row, or a segment of one row's
-// list.  The workgroups of a split row count themselves in as they end: all but the last
-// store their unnormalised O, reference max and weight sum; the last one waits for those
-// stores (the others do nothing but store by then, so the wait ends) and merges the
-// segments in list order, so the result does not depend on which workgroup came last.
+// list.  Every workgroup of a split row stores its unnormalised O, reference max and weight
+// sum, waits for its own stores and then takes the row's next ticket; the one that takes the
+// last merges the segments in list order, so the result does not depend on which it is.  No
+// workgroup waits for another: whatever the tickets hold, every workgroup ends.
 template <int D, int B, bool SPLIT>
 __global__ __launch_bounds__((Geo<D, B>::THREADS)) __attribute__((amdgpu_waves_per_eu(Geo<D, B>::OCC, Geo<D, B>::OCC)))
 void sparse_fa_fwd(AttnArgs a) {
@@ -734,28 +734,18 @@ void sparse_fa_fwd(AttnArgs a) {
         auto slot_of = [&](int i) {
           return a.split.partials + (int64_t)(slot0 + i) * (PAIRS + 1) * THREADS + tid;
         };
+        unsigned long long *to = slot_of(own);
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p)
+          store_dev(to + p * THREADS, oacc[p / 8][2 * (p % 8)], oacc[p / 8][2 * (p % 8) + 1]);
+        store_dev(to + PAIRS * THREADS, m_ref, l_tot);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
         if (tid == 0)
-          fetch_slot[0] = __hip_atomic_fetch_add(a.split.tickets + 2 * slot0, 1, __ATOMIC_RELAXED,
+          fetch_slot[0] = __hip_atomic_fetch_add(a.split.tickets + slot0, 1, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
-        if (fetch_slot[0] != nseg - 1) {
-          unsigned long long *to = slot_of(own);
-#pragma unroll
-          for (int p = 0; p < PAIRS; ++p)
-            store_dev(to + p * THREADS, oacc[p / 8][2 * (p % 8)], oacc[p / 8][2 * (p % 8) + 1]);
-          store_dev(to + PAIRS * THREADS, m_ref, l_tot);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-          __syncthreads();
-          if (tid == 0)
-            __hip_atomic_fetch_add(a.split.tickets + 2 * slot0 + 1, 1, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-          return;
-        }
-        if (tid == 0)
-          while (__hip_atomic_load(a.split.tickets + 2 * slot0 + 1, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT) != nseg - 1)
-            __builtin_amdgcn_s_sleep(1);
-        __syncthreads();
+        if (fetch_slot[0] != nseg - 1) return;
         float m_all = m_ref;
         for (int i = 0; i < nseg; ++i)
           if (i != own) m_all = fmaxf(m_all, load_dev(slot_of(i) + PAIRS * THREADS).x);
@@ -1094,8 +1084,7 @@ __device__ __forceinline__ void split_group_items(const SeqTable &st, const int3
                           (int64_t)I * (I + 1) / 2;
     const int u0 = atomicAdd(&n_unit, nseg - 1);
     const int slot = g * 2 * sp.extra + atomicAdd(&n_slot, nseg);
-    sp.tickets[2 * slot] = 0;
-    sp.tickets[2 * slot + 1] = 0;
+    sp.tickets[slot] = 0;
     for (int j = 0; j < nseg; ++j) {
       const int a = (int)((int64_t)cnt * j / nseg), b = (int)((int64_t)cnt * (j + 1) / nseg);
       const int u = j == 0 ? id : u0 + j - 1;

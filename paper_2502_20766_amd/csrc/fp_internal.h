@@ -110,7 +110,7 @@ constexpr int kSplitUnits = 2816;   // units per KV group: 8 B of key slots (a p
 struct SplitArgs {
   int4 *units;             // [Hkv][unit_cap] records {row, blocks, first block, second block}
   int4 *segs;              // [Hkv][unit_cap] {first list entry, first slot, segment, segments}
-  int32_t *tickets;        // [slots][2] per split row: workgroups that ended, and stored
+  int32_t *tickets;        // [slots] at a split row's first slot: its segments stored so far
   unsigned long long *partials;   // [slots] partial results of segments
   int32_t unit_cap;        // units per KV group, the unused last ones marked empty
   int32_t extra;           // units per KV group beyond its rows; 2 * extra slots

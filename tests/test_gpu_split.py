@@ -1,5 +1,8 @@
 """Short attention problems, whose rows are cut into segments over several workgroups: against
 the oracle at the edges of the cut, and with workspaces of every size."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -20,6 +23,18 @@ def test_preferred_workspace_covers_the_size_and_is_bounded():
         assert need <= best <= need + (256 << 20)
         if sum(seqlens) > 100000:
             assert best == need
+
+
+def test_no_kernel_waits_for_another_workgroup():
+    """A kernel that loops until another workgroup's counter arrives hangs the queue when two
+    calls share a workspace against the header's rule (the second call's preparation clears
+    the counter): results may be undefined then, an end may not.  No loop of the kernels tests
+    a device-scope load, and none sleeps."""
+    csrc = os.path.join(os.path.dirname(fpx.__file__), "csrc")
+    for name in sorted(os.listdir(csrc)):
+        text = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(csrc, name)).read(), flags=re.S)
+        assert not re.search(r"\b(while|for)\s*\([^{;]*__hip_atomic_load", text), name
+        assert "s_sleep" not in text, name
 
 
 # seqlens, hq, hkv, d, block, blocks listed per row: lengths around the shortest segment
