@@ -129,7 +129,15 @@ fp_status fp_attn_workspace_size(const fp_shape *shape, size_t *bytes);
 
 /* Workspace bytes with which fp_sparse_attn runs short problems fastest: the size above,
  * which is always enough, and room for the partial results of rows whose lists are divided
- * among several workgroups.  More workspace than this is not used.  Host only. */
+ * among several workgroups.  More workspace than this is not used, and it never exceeds
+ * FP_NOALLOC_SCRATCH_BYTES where the size above does not.  Host only.
+ * Which rows are divided, and where, follows from the shape, the counts of listed blocks of
+ * all rows of a KV group, and the workspace bytes up to this size.  It changes the low bits
+ * of a divided row's output (bf16 weights taken against another reference maximum, float32
+ * sums in another order; the error against exact results is the same), never from one call
+ * to the next with the same arguments.  With exactly fp_attn_workspace_size bytes no row is
+ * divided: an output row then depends on its own query, list, keys and values alone,
+ * whatever else is in the batch. */
 fp_status fp_attn_workspace_preferred(const fp_shape *shape, size_t *bytes);
 
 /* Host-only argument check used by fp_select (params != NULL) and fp_sparse_attn
@@ -159,7 +167,8 @@ fp_status fp_sparse_attn(const fp_shape *shape, const void *q, const void *k,
 
 /* fp_sparse_attn without a workspace argument, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc).  Same arguments, result and checks as fp_sparse_attn; the workspace is a
+ * hipMalloc).  Same arguments and checks as fp_sparse_attn, and the same result, bit for
+ * bit, as fp_sparse_attn with fp_attn_workspace_preferred bytes or more; the workspace is a
  * fixed FP_NOALLOC_SCRATCH_BYTES device array inside the library (one per GPU, held until
  * the process ends), so the call itself allocates nothing.  Problems whose
  * fp_attn_workspace_size exceeds FP_NOALLOC_SCRATCH_BYTES are rejected with

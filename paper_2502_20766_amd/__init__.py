@@ -76,7 +76,8 @@ def lib() -> ctypes.CDLL:
         h.fp_last_error.argtypes = []
         h.fp_last_error.restype = ctypes.c_char_p
         for name in ("fp_indices_size", "fp_select_workspace_size", "fp_attn_workspace_size",
-                     "fp_attn_workspace_preferred", "fp_validate", "fp_select", "fp_sparse_attn", "fp_sparse_attn_noalloc"):
+                     "fp_attn_workspace_preferred", "fp_validate", "fp_select", "fp_sparse_attn",
+                     "fp_sparse_attn_noalloc"):
             getattr(h, name).restype = ctypes.c_int
         _lib_handle = h
     return _lib_handle
@@ -138,7 +139,8 @@ def attn_workspace_size(shape: Shape) -> int:
 
 def attn_workspace_preferred(shape: Shape) -> int:
     """Workspace with which sparse_attn runs short problems fastest (attn_workspace_size is
-    always enough)."""
+    always enough, and with exactly that many bytes an output row does not depend, to the last
+    bit, on the rest of the batch)."""
     out = ctypes.c_size_t()
     _check(lib().fp_attn_workspace_preferred(ctypes.byref(shape.c), ctypes.byref(out)),
            "fp_attn_workspace_preferred")
@@ -256,7 +258,8 @@ def _check_indices(ind: Indices, shape: Shape):
 
 def sparse_attn(q, k, v, indices: Indices, out=None, workspace=None, stream=None):
     """O = A(Q, K, V, S) over the key-block lists in `indices`, with the softmax scale the
-    lists were selected with (indices.softmax_scale)."""
+    lists were selected with (indices.softmax_scale).  workspace: a uint8 tensor of at least
+    attn_workspace_size(indices.shape) bytes; attn_workspace_preferred bytes by default."""
     import torch
     for name, x in (("q", q), ("k", k), ("v", v)):
         _check_tensor(x, name, 3)
@@ -283,7 +286,8 @@ NOALLOC_SCRATCH_BYTES = 64 << 20     # FP_NOALLOC_SCRATCH_BYTES
 
 def sparse_attn_noalloc(q, k, v, indices: Indices, out, stream=None):
     """sparse_attn through fp_sparse_attn_noalloc: no workspace argument, the library's fixed
-    device scratch array instead (problems up to NOALLOC_SCRATCH_BYTES of workspace).
+    device scratch array instead (problems up to NOALLOC_SCRATCH_BYTES of workspace).  The
+    result is sparse_attn's with its default workspace, bit for bit.
     `out` is required: this call allocates nothing."""
     for name, x in (("q", q), ("k", k), ("v", v), ("out", out)):
         _check_tensor(x, name, 3)

@@ -3,8 +3,11 @@
 // Nothing here allocates device memory or synchronises: every call validates on the host,
 // carves the caller's workspace, and enqueues kernels on the caller's stream.
 #include <math.h>
+#include <stdint.h>
 #include <stdio.h>
 #include <string.h>
+
+#include <algorithm>
 
 #include "fp_internal.h"
 
@@ -161,11 +164,13 @@ size_t attn_layout(const fp_shape *sh, const Dims &dm) {
          align_up(8 * items) + align_up(16 * items);
 }
 
-// Split plan of a short attention problem in `room` (room_bytes of device workspace; null:
-// any size): fills *out (unit_cap = 0 when the problem is not short, or the room too small)
-// and returns the bytes it takes.
-size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, char *room,
-                  size_t room_bytes, fp::SplitArgs *out) {
+// Split plan of a short attention problem in `room` (room_bytes of device workspace after the
+// `base` bytes of attn_layout; null: any size): fills *out (unit_cap = 0 when the problem is
+// not short, or the room too small) and returns the bytes it takes.  A plan never takes more
+// than the fixed scratch array leaves after `base`, so that fp_sparse_attn_noalloc cuts the
+// same rows as fp_sparse_attn with all the room it can use.
+size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, size_t base,
+                  char *room, size_t room_bytes, fp::SplitArgs *out) {
   *out = fp::SplitArgs{};
   const int nb_total = st.nb_off[st.n_seq], G = hq / hkv;
   // resident workgroups of 256 CUs: two (head dim 128) or three waves per SIMD
@@ -203,11 +208,13 @@ size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, cha
   const int64_t share = (7 * (int64_t)slots / 10 + hkv - 1) / hkv;
   int64_t extra = share < most ? share : most;
   if (n_g + extra > fp::kSplitUnits) return 0;
-  if (room) {                                       // as much of the plan as the room holds
-    while (extra > 0 && layout(extra, nullptr) > room_bytes) extra = extra * 3 / 4;
-    if (layout(extra, nullptr) > room_bytes) return 0;
-    layout(extra, out);
-  }
+  // as much of the plan as the room holds
+  if (!room) room_bytes = SIZE_MAX;
+  if (base <= (size_t)FP_NOALLOC_SCRATCH_BYTES)
+    room_bytes = std::min(room_bytes, (size_t)FP_NOALLOC_SCRATCH_BYTES - base);
+  while (extra > 0 && layout(extra, nullptr) > room_bytes) --extra;
+  if (layout(extra, nullptr) > room_bytes) return 0;
+  if (room) layout(extra, out);
   return layout(extra, nullptr);
 }
 
@@ -256,8 +263,9 @@ fp_status fp_attn_workspace_preferred(const fp_shape *shape, size_t *bytes) {
   if (st != FP_OK) return st;
   if (!bytes) return FP_ERR_INVALID_ARG;
   fp::SplitArgs sp;
-  *bytes = attn_layout(shape, dm) + plan_split(dm.st, shape->num_q_heads, shape->num_kv_heads,
-                                                   shape->head_dim, shape->block, nullptr, 0, &sp);
+  const size_t base = attn_layout(shape, dm);
+  *bytes = base + plan_split(dm.st, shape->num_q_heads, shape->num_kv_heads, shape->head_dim,
+                             shape->block, base, nullptr, 0, &sp);
   return FP_OK;
 }
 
@@ -356,7 +364,8 @@ fp_status fp_sparse_attn(const fp_shape *shape, const void *q, const void *k, co
                                                 shape->block * shape->head_dim));
   a.sort_recs = (int4 *)((char *)a.sort_keys + align_up(8 * dm.nb_total * shape->num_q_heads));
   const size_t base = attn_layout(shape, dm);
-  plan_split(dm.st, a.hq, a.hkv, a.d, a.block, (char *)ws + base, ws_bytes - base, &a.split);
+  plan_split(dm.st, a.hq, a.hkv, a.d, a.block, base, (char *)ws + base, ws_bytes - base,
+             &a.split);
   hipError_t e = fp::launch_sparse_attn(a, (hipStream_t)stream);
   return e == hipSuccess ? FP_OK : hip_fail(e, "fp_sparse_attn");
 }

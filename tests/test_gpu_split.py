@@ -25,6 +25,22 @@ def test_preferred_workspace_covers_the_size_and_is_bounded():
             assert best == need
 
 
+def test_preferred_workspace_fits_the_scratch_array():
+    """What fp_sparse_attn_noalloc accepts it runs with the same cuts as fp_sparse_attn: the
+    preferred workspace is no larger than the scratch array wherever the required one is not."""
+    capped = 0
+    for hq, hkv, d in ((32, 32, 128), (32, 8, 128), (28, 4, 128), (64, 64, 64), (16, 16, 128),
+                       (8, 1, 64), (40, 40, 128), (1024, 1024, 64)):
+        for block in (64, 128):
+            for n in (1, 700, 1500, 2049, 3000, 4001, 5900, 8190, 9830, 16384):
+                sh = fpx.Shape([0, n], hq, hkv, d, block)
+                need, best = fpx.attn_workspace_size(sh), fpx.attn_workspace_preferred(sh)
+                if need <= fpx.NOALLOC_SCRATCH_BYTES:
+                    assert best <= fpx.NOALLOC_SCRATCH_BYTES, (hq, hkv, d, block, n)
+                    capped += best > fpx.NOALLOC_SCRATCH_BYTES - (1 << 20)
+    assert capped > 0
+
+
 def test_no_kernel_waits_for_another_workgroup():
     """A kernel that loops until another workgroup's counter arrives hangs the queue when two
     calls share a workspace against the header's rule (the second call's preparation clears
@@ -110,3 +126,50 @@ def test_split_rows_vs_oracle(case):
     # value) on top of the two sides' bf16 weights
     for o in outs[2:]:
         assert np.abs(o - outs[0]).max() <= O_MAX_ABS
+
+
+def _few_long_rows(shape, hq, device):
+    """Every fourth row lists every block, the others the first and their own."""
+    masks = {}
+    for s, nb in enumerate(shape.nb()):
+        m = np.tril(np.ones((nb, nb), bool))
+        m[np.arange(nb) % 4 != 3] = False
+        m[np.arange(nb), 0] = m[np.arange(nb), np.arange(nb)] = True
+        for h in range(hq):
+            masks[(s, h)] = m
+    return masks, fpx.indices_from_masks(shape, masks, device)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("hq,hkv", [(32, 32), (8, 2)])
+def test_results_by_workspace(hq, hkv):
+    """The fixed scratch array gives the default workspace's bits, also where the array limits
+    the cut (32 KV heads); the required workspace cuts no row, so a sequence's output has the
+    bits of the sequence alone."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    seqlens, d, block = (2300, 501), 128, 128
+    log(f"[split] by workspace, {hq} heads on {hkv}")
+    gen = torch.Generator("cuda")
+    gen.manual_seed(9)
+    q, k, v = (torch.randn(sum(seqlens), h, d, generator=gen, device="cuda").bfloat16()
+               for h in (hq, hkv, hkv))
+    shape = fpx.Shape([0, 2300, 2801], hq, hkv, d, block)
+    masks, idx = _few_long_rows(shape, hq, q.device)
+    o = fpx.sparse_attn(q, k, v, idx)
+    na = fpx.sparse_attn_noalloc(q, k, v, idx, torch.full_like(q, float("nan")))
+    torch.cuda.synchronize()
+    assert not bool((o != na).any())
+
+    def uncut(idx, *x):
+        ws = torch.empty(fpx.attn_workspace_size(idx.shape), dtype=torch.uint8, device=q.device)
+        return fpx.sparse_attn(*x, idx, workspace=ws)
+
+    plain = uncut(idx, q, k, v)
+    assert bool((o != plain).any())           # (rows of these lists are cut)
+    for s, (t0, t1) in enumerate(((0, 2300), (2300, 2801))):
+        alone = fpx.Shape([0, t1 - t0], hq, hkv, d, block)
+        ix = fpx.indices_from_masks(alone, {(0, h): masks[(s, h)] for h in range(hq)}, q.device)
+        got = uncut(ix, *(x[t0:t1].contiguous() for x in (q, k, v)))
+        torch.cuda.synchronize()
+        assert not bool((got != plain[t0:t1]).any())
