@@ -231,7 +231,7 @@ struct Row {
 };
 
 constexpr int kChunk = 16;   // consecutive ordered items kept together on one XCD
-constexpr int kMixItems = 8;    // at most this many items per workgroup: groups interleaved
+constexpr int kMixItems = 8;    // items per workgroup up to which groups are interleaved
 
 // Device-scope accesses of the split rows' partial results: they go past the L2 of the XCD,
 // so a workgroup on another XCD sees what was stored once the storing wave has waited for
@@ -1206,8 +1206,7 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
     else prepare(I64{}, I64{});
   }
   // Persistent grid: resident workgroups (a multiple of 8, one share per XCD), no more than
-  // there are items; groups are interleaved on an XCD when there are at most kMixItems items
-  // per workgroup.
+  // there are items.
   const int64_t total = n_g * a.hkv;
   auto attend = [&](auto dc, auto bc) {
     constexpr int D = decltype(dc)::value, B = decltype(bc)::value;
@@ -1216,12 +1215,19 @@ hipError_t launch_sparse_attn(const AttnArgs &a, hipStream_t stream) {
                          dim3(Geo<D, B>::THREADS), 0, stream, a);
       return;
     }
-    // with few rows per workgroup (`mix`) two waves per SIMD: a third one slows the longest
-    // rows, which then decide (64 heads of 64, 8k tokens, block 64: 357 us against 329)
-    const int full = Geo<D, B>::WG_PER_CU * cus;
+    // Up to kMixItems rows per workgroup of the two-wave grid, two waves per SIMD and groups
+    // interleaved: a third wave slows the longest rows, which then decide (64 heads of 64, 8k
+    // tokens, block 64: 357 us against 329).  Above that as many waves as fit, groups still
+    // interleaved up to kMixItems rows per workgroup of that grid at block 128: over every
+    // block 745 us against 794 one group after the other (64 heads of 64, 8900 tokens) and
+    // 1291 against 1352 (32 heads, 17k), over a quarter of the blocks within 3%.  At block 64
+    // that gains 2-10% over every block and loses 2-6% over a quarter (32 heads on 32, 22k
+    // tokens: 847 us one group after the other, 896 interleaved), which selected lists are
+    // nearer to.  (The two grids are the same at head dim 128.)
+    const int full = Geo<D, B>::WG_PER_CU * cus, two = 512 / Geo<D, B>::THREADS * cus;
     AttnArgs args = a;
-    args.mix = total <= (int64_t)kMixItems * full;
-    const int resident = args.mix ? 512 / Geo<D, B>::THREADS * cus : full;
+    args.mix = total <= (int64_t)kMixItems * (B == 128 ? full : two);
+    const int resident = total <= (int64_t)kMixItems * two ? two : full;
     const int grid = (int)std::min<int64_t>(resident / 8 * 8, (total + 7) / 8 * 8);
     hipLaunchKernelGGL((sparse_fa_fwd<D, B, false>), dim3(grid), dim3(Geo<D, B>::THREADS), 0, stream,
                        args);
