@@ -81,3 +81,42 @@ def test_ties_at_the_threshold_take_the_lowest_ids(n):
                         spec.min_budget, force_pattern=0)
     for h in range(2):
         np.testing.assert_array_equal(masks[(0, h)], ref[0][h]["mask"])
+
+
+@pytest.mark.parametrize("n", [16384, 16385])
+@pytest.mark.parametrize("kind", ["map", "first lines", "late lines"])
+def test_ties_over_many_steps_take_the_lowest_ids(kind, n):
+    """Runs of equal units that the tie break walks in several steps of 1024, the cut in a late
+    one.  Keys outside a window have logit -128, weight 0 in float32; the others logit 0, and
+    their number is a power of two, so every score is exact in any order of its sums.
+    map: the first 16 key blocks, 1/16 in every longer row (about 1600 of 1800 units taken, over
+    6600 ids).  lines: 8192 keys, at the start and at the end: 7373 of the 8192 vertical lines
+    and of the slash lines that meet them in every representative row."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import numpy as np
+    import oracle
+    import paper_2502_20766_amd as fpx
+    log(f"[select ties] {kind} {n}")
+    spec = BASE.with_seqlens((n,), f"ties-{n}").with_params(hq=2, hkv=1, head_kinds=("vs", "qa"),
+                                                            min_budget=1)
+    layer = synth.make_layer(spec)
+    layer.q[:], layer.k[:] = 0.0, 0.0
+    layer.q[..., 0], layer.k[..., 0] = 16.0, -64.0
+    last = n - min(spec.block, n)                 # first representative row
+    lo, hi = {"map": (0, 2048), "first lines": (0, 8192), "late lines": (last - 8192, last)}[kind]
+    layer.k[lo:hi, :, 0] = 0.0
+    force = 0 if kind == "map" else 1
+    q, k, _ = to_device(layer)
+    idx = fpx.select(q, k, layer.cu_seqlens, spec.gamma, spec.tau, spec.min_budget,
+                     force_pattern=force)
+    masks = fpx.masks_from_indices(idx)
+    units = idx.units.cpu().numpy().reshape(2, 2)
+    ref = oracle.select(layer.q, layer.k, layer.cu_seqlens, spec.block, spec.gamma, spec.tau,
+                        spec.min_budget, force_pattern=force)
+    for h in range(2):
+        want = ref[0][h]["units"]
+        log(f"  units {units[h].tolist()}, oracle {tuple(want)}")
+        assert units[h, 0] == want[0] and (kind == "map" or units[h, 1] == want[1])
+        assert want[0] > (1600 if kind == "map" else 7000)
+        np.testing.assert_array_equal(masks[(0, h)], ref[0][h]["mask"])
