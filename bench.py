@@ -549,7 +549,7 @@ def main():
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(attn_tflops / PEAK_BF16_TFLOPS, 4),
                      "traffic": attn_traffic_bytes(spec.name),
-                     "kernel": f"sparse_fa_fwd<{spec.d}, {spec.block}>",
+                     "kernel": f"sparse_fa_fwd<{spec.d}, {spec.block}, false>",
                      "per_launch_flop": f_comp,
                      "per_launch_flop_causal_exact": f_exact,
                      "timed": "whole fp_sparse_attn call (work-order set-up + attention "

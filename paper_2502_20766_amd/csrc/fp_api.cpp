@@ -131,7 +131,7 @@ size_t select_layout(const fp_shape *sh, const Dims &dm, char *base, fp::SelectA
   char *vs_marks = take(4 * hq * dm.nb_total);
   char *flat = take(sizeof(float) * hq * dm.tri_total);
   char *sel = take(sizeof(fp::SelState) * problems);
-  char *hist_cnt = take(sizeof(uint32_t) * problems * fp::kHistBuckets);
+  char *hist_cnt = take(sizeof(uint32_t) * problems * fp::kHistCounts);
   char *hist_mass = take(sizeof(unsigned long long) * problems * fp::kHistBuckets);
   if (a) {
     a->chunk_stats = (float2 *)chunk_stats;

@@ -16,6 +16,7 @@ constexpr int kScoreChunkMin = 256;
 // workgroups of the line-sum kernel wanted before the chunk is shortened (4 per CU)
 constexpr int kScoreWorkgroups = 1024;
 constexpr int kHistBuckets = 2048;     // radix-select digit: 11 bits
+constexpr int kHistCounts = 1024;      // last digit (10 bits), the only one with counts
 
 // Per-call table of packed sequences, passed by value to every kernel.
 struct SeqTable {
@@ -65,7 +66,7 @@ struct SelectArgs {
                            // rows), diagonal (partial last row), diagonal + 1
   float *flat;             // [Hq][TRI]
   struct SelState *sel;    // [n_seq][Hq][2]
-  uint32_t *hist_cnt;      // [n_seq][Hq][2][kHistBuckets]
+  uint32_t *hist_cnt;      // [n_seq][Hq][2][kHistCounts]
   unsigned long long *hist_mass;  // [n_seq][Hq][2][kHistBuckets]
   // outputs
   int32_t *kb_idx;
@@ -85,7 +86,6 @@ struct SelState {
   uint32_t cnt_above;             // number of keys above the current digit range
   uint32_t prefix;                // key bits fixed so far
   uint32_t key;                   // final threshold key
-  uint32_t need_eq;               // units with key == `key` to take (lowest ids first)
   int32_t idcut;                  // last id taken among key == `key`
   int32_t k;                      // units selected
   int32_t mode;                   // 0 active, 1 take all, 2 inactive (other pattern)

@@ -105,7 +105,7 @@ __device__ __forceinline__ bool is_selected(const SelState &S, float x, int id) 
 // workgroup's additions waited for before its ticket.
 template <int PASS>
 __global__ __launch_bounds__(256) void sel_hist(SelectArgs a) {
-  constexpr int NB = PASS == 2 ? 1024 : kHistBuckets;      // digits of this pass
+  constexpr int NB = PASS == 2 ? kHistCounts : kHistBuckets;      // digits of this pass
   constexpr int shift = PASS == 0 ? 21 : (PASS == 1 ? 10 : 0);
   __shared__ unsigned long long mass[NB];
   __shared__ uint32_t cnt[PASS == 2 ? NB : 1];
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void sel_hist(SelectArgs a) {
   }
   __syncthreads();
   unsigned long long *hm = a.hist_mass + (int64_t)p * kHistBuckets;
-  uint32_t *hc = a.hist_cnt + (int64_t)p * kHistBuckets;
+  uint32_t *hc = a.hist_cnt + (int64_t)p * kHistCounts;
   for (int b = tid; b < NB; b += 256) {
     if (mass[b]) atomicAdd(&hm[b], mass[b]);
     if constexpr (PASS == 2)
@@ -234,7 +234,6 @@ __global__ __launch_bounds__(256) void sel_hist(SelectArgs a) {
         T.key = T.prefix;
         const unsigned long long f = bm[i] / bc[i];   // equal keys carry equal mass
         const unsigned long long need = (T.thr - run + f - 1) / f;
-        T.need_eq = (uint32_t)need;
         T.k = (int32_t)(runc + need);
         T.idcut = 0x7FFFFFFF;
         if (need < bc[i]) {
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(NT) void sel_small(SelectArgs a) {
   }
   S.key = S.prefix;
   const unsigned long long f = to_fx(__uint_as_float(S.key));
-  S.need_eq = (uint32_t)((S.thr - S.mass_above + f - 1) / f);
+  const uint32_t need = (uint32_t)((S.thr - S.mass_above + f - 1) / f);   // units of the key
   // units above the key, and of the key (both at most kSmallUnits)
   uint32_t c = 0u;
 #pragma unroll
@@ -398,10 +397,10 @@ __global__ __launch_bounds__(NT) void sel_small(SelectArgs a) {
   for (int k = 0; k < NW; ++k) c += wcount[k];
   S.cnt_above = c >> 16;
   const uint32_t n_eq = c & 0xFFFFu;
-  S.k = (int32_t)(S.cnt_above + S.need_eq);
+  S.k = (int32_t)(S.cnt_above + need);
   S.idcut = 0x7FFFFFFF;
   // lowest-id tie break, when some but not all units of the key are taken
-  if (S.need_eq < n_eq) {
+  if (need < n_eq) {
     uint32_t running = 0;
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -418,7 +417,7 @@ __global__ __launch_bounds__(NT) void sel_small(SelectArgs a) {
         chunk += wcount[k];
       }
       const uint32_t rank = running + before + (uint32_t)__popcll(bal & __lanemask_lt());
-      if (f && rank + 1 == S.need_eq) found = i;
+      if (f && rank + 1 == need) found = i;
       running += chunk;
     }
     __syncthreads();
@@ -529,8 +528,7 @@ __global__ __launch_bounds__(1024) void convert_tiles(SelectArgs a) {
   const int s = blockIdx.x / a.hq, h = blockIdx.x % a.hq;
   const int slice = blockIdx.y, n_slices = gridDim.y;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int tok0 = a.st.cu[s];
-  const int n = a.st.cu[s + 1] - tok0;
+  const int n = a.st.cu[s + 1] - a.st.cu[s];
   const int b = a.block;
   const int nb = a.st.nb_off[s + 1] - a.st.nb_off[s];
   const int pat = a.pattern[s * a.hq + h];
@@ -539,8 +537,6 @@ __global__ __launch_bounds__(1024) void convert_tiles(SelectArgs a) {
   const SelState S0 = a.sel[p0];
   const SelState S1 = a.sel[p0 + 1];
   const float *flat = a.flat + (int64_t)h * a.tri_total + a.st.tri_off[s];
-  (void)tok0;
-  (void)n;
   if (slice * 16 >= nb) return;                 // no row of this (sequence, head) here
 
   if (vs && a.marks_inline) {

@@ -48,7 +48,7 @@ __device__ __forceinline__ void init_problems(const SelectArgs &a, int s, int h,
   const int p0 = (s * a.hq + h) * 2;
   if (!a.small)
     for (int b = tid; b < 2 * kHistBuckets; b += nt) {
-      a.hist_cnt[(int64_t)p0 * kHistBuckets + b] = 0u;
+      if (b < 2 * kHistCounts) a.hist_cnt[(int64_t)p0 * kHistCounts + b] = 0u;
       a.hist_mass[(int64_t)p0 * kHistBuckets + b] = 0ull;
     }
   if (!a.marks_inline) {
