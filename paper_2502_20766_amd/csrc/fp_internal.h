@@ -93,10 +93,13 @@ struct SelState {
 };
 
 // The split grid is taken for at most this many tenths of a row per resident workgroup.
-// Where the line lies (attention, us, other grid -> split grid): block 128, 2.0 rows
-// (32 heads, 4k tokens) 142 -> 128, 2.9 (6k) 256 -> 246, 4.0 (8k) 344 -> 361; block 64,
-// 4.0 rows (32 heads, 8k) 316 -> 292, 4.6 (64 heads of 64, 7k) 377 -> 310, 4.9 (32 heads,
-// 10k) 540 -> 546.
+// Where the line lies (attention over selected lists, us, other grid -> split grid; single
+// runs differ by 3-10%): block 128, head dim 128, 2.0 rows (32 heads, 4k tokens) 143 -> 121,
+// 2.9 (6k) 251 -> 250, 3.4 (7k) 320 -> 318, 5.0 (10k) 516 -> 544; head dim 64, 3.0 rows (64
+// heads, 4500) 208 -> 170, 3.6 (5500) 229 -> 194, 4.6 (7k) 375 -> 347, 6.2 (9500) 549 -> 549,
+// so on the safe side there; block 64, head dim 128, 4.0 rows (32 heads, 8k) 282 -> 223, 4.8
+// (9800) 460 -> 496; head dim 64, 4.6 (64 heads, 7k) 374 -> 293, 5.5 (8500) 517 -> 437, 6.9
+// (10500) 586 -> 541.
 constexpr int kSplitRows128 = 30;
 constexpr int kSplitRows64 = 48;
 // Shortest segment that a longer list is cut into: 3, 4 and 6 blocks measure the same within

@@ -88,7 +88,7 @@ __device__ __forceinline__ void pool_qhat(const SelectArgs &a, int s, int h, flo
 // block J: out(J, scale * q_bar . K_bar_J, a_hat[J]).  The lanes of a block read its pooled
 // key (16-byte pieces) and its line scores (lane l tokens l, l + 16, ...) coalesced and
 // whatever the sequence's alignment, all loads in flight, and add up by a fixed butterfly
-// (a_hat in double).  One thread per block, as before, waited for every load of a sequence
+// (a_hat in double).  One thread per block waits for every load of a sequence
 // that does not start on a 16-byte boundary in turn: 109 us for 64 ragged sequences.
 template <int D, int NT, typename F>
 __device__ __forceinline__ void block_terms(const SelectArgs &a, int s, int h, int J0, int J1,
@@ -393,8 +393,10 @@ __global__ __launch_bounds__(kThreads) void qa_softmax(SelectArgs a) {
 
 // Sequences of few blocks, and either very few or so many (sequence, head) pairs that
 // workgroups of 1024 threads come one or two to a CU: 256 threads (64 sequences of 8 heads of
-// up to 18 blocks: pattern search 18.1 -> 11.0 us, logits 30.3 -> 14.6; 32 heads of 32 blocks are
-// 2.4 us faster with 1024).
+// up to 18 blocks: pattern search 18.1 -> 11.0 us, logits 30.3 -> 14.6).  The whole selection
+// with 1024 threads and with 256: up to 17 blocks 65.0 and 66.0 us at 32 pairs, 79.3 and 79.5
+// at 128, 128 and 126 at 256, 123 and 114 at 264, 187 and 168 at 512; up to 32 blocks 74 and
+// 77 at 32, 118 and 120 at 128, 180 and 181 at 256, 185 and 179 at 264, 320 and 302 at 512.
 static bool small_heads(const SelectArgs &a) {
   return a.st.max_nb <= 16 || (a.st.max_nb <= kQtSmall && a.st.n_seq * a.hq > 256);
 }

@@ -6,16 +6,19 @@
 //   a_v[j] = sum_r A_hat[r, j] / b'            (vertical lines, Algorithm 3)
 //   a_s[o] = sum_r A_hat[r, i_r - o] / b'      (slash lines, offset o = i - j)
 // A_hat is never stored: pass 1 computes each row's max and sum of exp per chunk of
-// 1024 keys (512 or 256 for short problems, so that the passes still fill the GPU), a
-// combine kernel merges the chunks, pass 2 recomputes the scores tile by tile, sums the
-// columns in registers (one key per lane) and the diagonals through an LDS tile.  Every
-// sum is in a fixed order (no float atomics), so results are bit-reproducible for a given
-// shape.  Each pass-2 workgroup owns the slash offsets whose last-row key falls in its
-// chunk and recomputes the 128 keys before the chunk so that it sees those diagonals whole.
+// 1024 keys (512 or 256 for short problems, so that the passes still fill the GPU); pass 2
+// merges them in chunk order where no sequence has more than kMergeInline chunks (a combine
+// kernel before it does otherwise), recomputes the scores tile by tile, sums the columns in
+// registers (one key per lane) and the diagonals through an LDS tile.  Every sum is in a
+// fixed order (no float atomics), so results are bit-reproducible for a given shape.  A
+// pass-2 workgroup takes a chunk, or on short problems a part of one of kLinePart keys or
+// more; it owns the slash offsets whose last-row key falls in its keys and recomputes the
+// block_size keys before them so that it sees those diagonals whole.
 //
 // Block pooling (avgpool with window block_size, aligned at token 0 of each sequence): K̄
-// (every KV head) is summed by pass 1 from the K tiles it streams anyway, Q̄ (query-aware
-// heads only) by a separate streaming kernel.
+// (every KV head) is summed by pass 1 from the K tiles it streams anyway.  Q̄ is pooled for
+// query-aware heads by a separate streaming kernel, or, on layers whose Q is small enough
+// for it (pool_inline), for every head by workgroups of pass 2.
 #include <algorithm>
 #include <type_traits>
 

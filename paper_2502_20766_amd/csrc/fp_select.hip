@@ -98,9 +98,8 @@ __device__ __forceinline__ bool is_selected(const SelState &S, float x, int id) 
 // problem to do so (a ticket in the problem's state) finds the digit whose bucket carries the
 // cumulative mass across the threshold.  Counts are not taken per digit: pass 2 counts the
 // units above its range in registers and the few units inside it by their last digit, which
-// halves the LDS atomics that bound pass 0.  The scan and the tie break had launches of their
-// own before: 51 us for the seven launches at 32 heads and 32k tokens (92 at 128k), 36 (78) for
-// these three.
+// halves the LDS atomics that bound pass 0.  With the scan and the tie break in launches of
+// their own the select took 51 us at 32 heads and 32k tokens (92 at 128k), so 36 (78).
 // The histograms and the ticket are shared between XCDs: device-scope atomics and loads, each
 // workgroup's additions waited for before its ticket.
 template <int PASS>
@@ -296,7 +295,9 @@ __global__ __launch_bounds__(256) void sel_hist(SelectArgs a) {
 // A thread holds its E scores (units tid + NT e) in registers over the passes.  The LDS
 // atomics bound it (many scores share a bucket), so the histogram holds masses only: units
 // of the threshold key all carry that key's own mass, and the units above it are counted
-// once at the end (32 heads: 15.3 -> 11.7 us at 4k tokens, 35.5 -> 26.4 at 16k).
+// once at the end (32 heads: 15.3 -> 11.7 us at 4k tokens, 35.5 -> 26.4 at 16k).  16 scores
+// per thread take 135 registers in workgroups of 256 threads (three of them a CU) and spill
+// 12 at the 128 that workgroups of 1024 are held to.
 constexpr int kSmallUnits = 16384;    // largest problem (units) taken by sel_small
 
 template <int NT, int E>
@@ -1021,8 +1022,10 @@ hipError_t launch_select_pipeline(const SelectArgs &args, hipStream_t stream) {
   if (a.vs_granularity == 1)
     hipLaunchKernelGGL(pool_lines, dim3((a.nb_total + 3) / 4, a.hq), dim3(256), 0, stream, a);
   if (a.small) {
-    // many small problems: eight workgroups of 256 threads a CU instead of two of 1024
-    // (64 sequences of 8 heads: 39.4 -> 19.3 us)
+    // many small problems: three workgroups of 256 threads a CU instead of one of 1024 (64
+    // sequences of 8 heads: 39.4 -> 19.3 us).  The line is on the safe side: the selection of
+    // packed sequences of up to 17 blocks takes 130 us with 1024 threads and 114 with 256 at
+    // 528 problems, 128 and 118 at 512, 79 and 78 at 256, 65 and 63 at 64.
     if (max_units <= 4096 && problems > 512)
       hipLaunchKernelGGL((sel_small<256, 16>), dim3(problems), dim3(256), 0, stream, a);
     else if (max_units <= 4096)
