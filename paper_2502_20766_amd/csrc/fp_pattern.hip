@@ -88,8 +88,9 @@ __device__ __forceinline__ void pool_qhat(const SelectArgs &a, int s, int h, flo
 // block J: out(J, scale * q_bar . K_bar_J, a_hat[J]).  The lanes of a block read its pooled
 // key (16-byte pieces) and its line scores (lane l tokens l, l + 16, ...) coalesced and
 // whatever the sequence's alignment, all loads in flight, and add up by a fixed butterfly
-// (a_hat in double).  One thread per block waits for every load of a sequence
-// that does not start on a 16-byte boundary in turn: 109 us for 64 ragged sequences.
+// (a_hat in double).  One thread per block waits for every
+// load of a sequence that does not start on a 16-byte boundary in turn: 109 us for 64 ragged
+// sequences.
 template <int D, int NT, typename F>
 __device__ __forceinline__ void block_terms(const SelectArgs &a, int s, int h, int J0, int J1,
                                             const float *qbar, F out) {
