@@ -175,6 +175,18 @@ def _stream_ptr(stream):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+def _workspace(n, device, stream):
+    """n bytes for one call on `stream`, from that stream's memory: nothing pending on another
+    stream still uses them, and nothing of another stream gets them while the call runs."""
+    import torch
+    if stream is None:
+        return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(max(n, 1), dtype=torch.uint8, device=device)
+
+
 def _check_tensor(x, name, ndim, dtype=None):
     import torch
     dtype = torch.bfloat16 if dtype is None else dtype
@@ -232,7 +244,7 @@ def select(q, k, cu_seqlens, gamma, tau, min_budget=8, block=128, softmax_scale=
                vs_granularity)
     ws_bytes = select_workspace_size(shape, p)
     if workspace is None:
-        workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=q.device)
+        workspace = _workspace(ws_bytes, q.device, stream)
     if out is None:
         out = empty_indices(shape, q.device)
     _check_indices(out, shape)
@@ -270,8 +282,7 @@ def sparse_attn(q, k, v, indices: Indices, out=None, workspace=None, stream=None
     check_shapes(shape, q=q.shape, k=k.shape, v=v.shape, o=out.shape)
     _check_indices(indices, shape)
     if workspace is None:
-        ws_bytes = attn_workspace_preferred(shape)
-        workspace = torch.empty(max(ws_bytes, 1), dtype=torch.uint8, device=q.device)
+        workspace = _workspace(attn_workspace_preferred(shape), q.device, stream)
     ic = indices.c()
     _check(lib().fp_sparse_attn(ctypes.byref(shape.c), ctypes.c_void_p(q.data_ptr()),
                                 ctypes.c_void_p(k.data_ptr()), ctypes.c_void_p(v.data_ptr()),

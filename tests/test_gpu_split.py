@@ -173,3 +173,37 @@ def test_results_by_workspace(hq, hkv):
         got = uncut(ix, *(x[t0:t1].contiguous() for x in (q, k, v)))
         torch.cuda.synchronize()
         assert not bool((got != plain[t0:t1]).any())
+
+
+@pytest.mark.gpu
+def test_default_workspaces_come_from_the_stream_of_the_call(monkeypatch):
+    """A workspace taken from the current stream's memory and used on another stream could still
+    be in use there, or be given out again while the call runs."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    gen = torch.Generator("cuda")
+    gen.manual_seed(4)
+    q, k, v = (torch.randn(1024, 2, 64, generator=gen, device="cuda").bfloat16() for _ in range(3))
+    out = fpx.empty_indices(fpx.Shape([0, 1024], 2, 2, 64), q.device)
+    o, side = torch.empty_like(q), torch.cuda.Stream()
+    ref = fpx.sparse_attn(q, k, v, fpx.select(q, k, [0, 1024], 0.9, 0.1, 1))
+    torch.cuda.synchronize()
+    seen, empty = [], torch.empty
+
+    def spy(*a, **kw):
+        seen.append(torch.cuda.current_stream())
+        return empty(*a, **kw)
+
+    monkeypatch.setattr(torch, "empty", spy)
+
+    class Handle:                              # what a caller with a raw handle passes
+        cuda_stream = side.cuda_stream
+
+    for stream in (side, Handle()):
+        fpx.select(q, k, [0, 1024], 0.9, 0.1, 1, out=out, stream=stream)
+        fpx.sparse_attn(q, k, v, out, out=o, stream=stream)
+        torch.cuda.synchronize()
+        assert len(seen) == 2 and all(s.cuda_stream == side.cuda_stream for s in seen)
+        assert torch.cuda.current_stream() == torch.cuda.default_stream()
+        assert not bool((o != ref).any())
+        seen.clear()
