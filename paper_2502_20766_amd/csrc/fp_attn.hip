@@ -63,9 +63,8 @@ struct Geo {
   // (163 used): 64 heads at 32k tokens 1873 -> 1760 us (759 -> 808 TFLOP/s), block 64 1522 ->
   // 1411.  Four waves at block 128 spill 60 registers; at block 64 they fit (123 registers)
   // and gained nothing (16k tokens 823 -> 842 us, every block 2757 -> 2757).  Head dim 128
-  // needs 233 registers;
-  // 32-key stages fit 168 (5 spilled), which gained 1.5% at 128k tokens and lost 1.5% over
-  // every block at 16k and 40% at 4k.
+  // needs 233 registers; 32-key stages fit 168 (5 spilled), which gained 1.5% at 128k tokens
+  // and lost 1.5% over every block at 16k and 40% at 4k.
   static constexpr int OCC = D == 64 ? 3 : 2;
   static constexpr int WG_PER_CU = 256 * OCC / THREADS;
 };
