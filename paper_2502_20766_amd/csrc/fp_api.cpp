@@ -212,6 +212,7 @@ size_t plan_split(const fp::SeqTable &st, int hq, int hkv, int d, int block, siz
   if (!room) room_bytes = SIZE_MAX;
   if (base <= (size_t)FP_NOALLOC_SCRATCH_BYTES)
     room_bytes = std::min(room_bytes, (size_t)FP_NOALLOC_SCRATCH_BYTES - base);
+  extra = (int64_t)std::min<size_t>((size_t)extra, room_bytes / (size_t)(2 * hkv * part));
   while (extra > 0 && layout(extra, nullptr) > room_bytes) --extra;
   if (layout(extra, nullptr) > room_bytes) return 0;
   if (room) layout(extra, out);
